@@ -235,6 +235,7 @@ struct trt_batch {
     int ndescs2;  // two-step descriptors (class-1 members)
     bool deep2;   // two-step launches load two rows ahead
     int k2;       // time steps per class-1 launch: 2, or 3 (FP32, steps_per_sweep 3)
+    int64_t steps;  // time steps since the tables were built
     int parity2;  // class-1 launches and one-step sweeps of class 1, mod 2
     hipStream_t cap_stream;
     hipGraphExec_t graphs[kMaxGraphLevels];  // level k: 2^(k+1) batched sweeps
@@ -466,7 +467,9 @@ void fill_desc(InstDesc &d, const trt_problem *p, void *f_a, void *f_b) {
     d.gx = p->gx;
     d.gy = p->gy;
     d.xbc = p->x_boundary == TRT_X_INFLOW_OUTFLOW ? 1 : 0;
-    d.pad2_ = 0;
+    d.cls = 0;
+    d.time0 = 0;
+    d.partials = nullptr;
     d.u_in = d.xbc ? p->u_in : 0.0;
     d.rho_in = d.xbc ? p->rho_in : 1.0;
     d.rho_out = d.xbc ? p->rho_out : 1.0;
@@ -516,6 +519,7 @@ trt_status trt_create(const trt_problem *p, void *f_a, void *f_b, void *hip_stre
         delete s;
         return fail_hip(e, "hipMalloc(scratch)");
     }
+    d.partials = s->scratch;
     if (needs_links(p)) {
         e = hipMalloc((void **)&s->links, link_alloc_bytes(p->nx, p->ny));
         if (e == hipSuccess) {
@@ -910,6 +914,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
         InstDesc &d = descs[k];
         d = b->sims[k]->desc;
         d.cur = b->sims[k]->cur;
+        d.time0 = b->sims[k]->time;
         trt::tile(d, b->launch, b->sims[k]->prob.storage);
     }
     if (b->launch.rows_per_wave <= 0 && b->launch.batch_items > 0) {
@@ -943,6 +948,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
                                     : trt::tb2_eligible(descs[k], b->sims[k]->prob.storage))
                             ? 1
                             : 0;
+    for (size_t k = 0; k < n; ++k) descs[k].cls = b->two[k];
     const int valid2 = b->k2 == 3 ? trt::kTb3Valid : trt::kTb2Valid;
     const auto cost = [&](const int4 &it) {
         // two-step items (it.w == 2) index the two-step descriptors, which
@@ -1050,6 +1056,7 @@ static trt_status batch_build(trt_batch *b) {
     sg.pending = true;
     b->parity = 0;
     b->parity2 = 0;
+    b->steps = 0;
     release_graphs(b->graphs);
     return TRT_OK;
 }
@@ -1154,6 +1161,7 @@ trt_status trt_batch_get_tuning(const trt_batch *b, trt_tuning *t) {
 }
 
 static void batch_sync_members(trt_batch *b, int64_t steps, int64_t flips0, int64_t flips1) {
+    b->steps += steps;
     for (size_t k = 0; k < b->sims.size(); ++k) {
         trt_sim *s = b->sims[k];
         s->time += steps;
@@ -1293,10 +1301,12 @@ trt_status trt_batch_step(trt_batch *b, int64_t nsteps) {
 trt_status trt_batch_diagnostics(trt_batch *b, double *out) {
     if (!b) return fail(TRT_EINVAL, "batch handle is NULL");
     if (!out) return fail(TRT_EINVAL, "out is NULL");
-    for (size_t k = 0; k < b->sims.size(); ++k) {
-        trt_status st = trt_diagnostics(b->sims[k], out + k * TRT_NDIAG);
-        if (st != TRT_OK) return st;
-    }
+    const size_t n = b->sims.size();
+    int64_t most = 0;
+    for (const trt_sim *s : b->sims) most = std::max(most, (int64_t)s->desc.nx * s->desc.ny);
+    TRT_HIP(trt::launch_diagnostics_batch(b->d_descs, (int)n, most, b->storage, b->parity,
+                                          b->nitems2 > 0 ? b->parity2 : b->parity, b->steps, out,
+                                          b->stream));
     return TRT_OK;
 }
 

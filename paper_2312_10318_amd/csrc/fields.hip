@@ -179,6 +179,14 @@ __device__ __forceinline__ void acc_merge(Acc &a, const Acc &b) {
     a.v[6] = fmin(a.v[6], b.v[6]);
 }
 
+// Workgroups of a reduction over `nodes` nodes: one per kDiagThreads nodes,
+// at most kDiagBlocks.  The count depends on the lattice alone, so a lattice
+// reduces in one order whatever call asks.
+__host__ __device__ __forceinline__ int diag_blocks(int64_t nodes) {
+    const int64_t b = (nodes + kDiagThreads - 1) / kDiagThreads;
+    return (int)(b < kDiagBlocks ? b : kDiagBlocks);
+}
+
 // Fixed-shape reduction: thread -> nodes is a fixed grid-stride map and the
 // tree below has a fixed order, so the result is bitwise reproducible.
 __device__ void block_reduce(Acc &a) {
@@ -203,13 +211,13 @@ __device__ void block_reduce(Acc &a) {
 }
 
 template <int ST>
-__global__ __launch_bounds__(kDiagThreads) void diag_kernel(InstDesc d, int srcsel,
-                                                           double *__restrict__ partials) {
+__device__ __forceinline__ void diag_block(const InstDesc &d, int srcsel, int block, int blocks,
+                                           double *__restrict__ partials) {
     Acc a;
     acc_init(a);
     const int64_t n = (int64_t)d.nx * d.ny;
-    for (int64_t k = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x; k < n;
-         k += (int64_t)kDiagBlocks * kDiagThreads) {
+    for (int64_t k = (int64_t)block * kDiagThreads + threadIdx.x; k < n;
+         k += (int64_t)blocks * kDiagThreads) {
         const int y = (int)(k / d.nx), x = (int)(k - (int64_t)y * d.nx);
         Moments<double, Store<ST>::shifted> m;
         if (node_moments<ST>(d, srcsel, x, y, m)) continue;
@@ -229,22 +237,59 @@ __global__ __launch_bounds__(kDiagThreads) void diag_kernel(InstDesc d, int srcs
     }
     block_reduce(a);
     if (threadIdx.x == 0)
-        for (int j = 0; j < TRT_NDIAG; ++j) partials[blockIdx.x * TRT_NDIAG + j] = a.v[j];
+        for (int j = 0; j < TRT_NDIAG; ++j) partials[block * TRT_NDIAG + j] = a.v[j];
 }
 
-__global__ void diag_final_kernel(const double *__restrict__ partials, double *__restrict__ out,
-                                  double time) {
-    if (threadIdx.x != 0) return;
+// The partials' sum.  One workgroup: thread t takes partials t and t + 256,
+// then the workgroup's tree.  (One thread reading all 512 partials in turn
+// took 63 us, a serial chain of loads; this takes about 4.)
+__device__ __forceinline__ void diag_final(const double *__restrict__ partials, int blocks,
+                                           double *__restrict__ out, double time) {
     Acc a;
     acc_init(a);
-    for (int b = 0; b < kDiagBlocks; ++b) {
+    for (int b = threadIdx.x; b < blocks; b += kDiagThreads) {
         Acc o;
+#pragma unroll
         for (int j = 0; j < TRT_NDIAG; ++j) o.v[j] = partials[b * TRT_NDIAG + j];
         acc_merge(a, o);
     }
+    block_reduce(a);
+    if (threadIdx.x != 0) return;
     if (a.v[5] == 0.0 || a.v[6] == INFINITY) a.v[6] = 0.0;
     a.v[7] = time;
     for (int j = 0; j < TRT_NDIAG; ++j) out[j] = a.v[j];
+}
+
+template <int ST>
+__global__ __launch_bounds__(kDiagThreads) void diag_kernel(InstDesc d, int srcsel,
+                                                           double *__restrict__ partials) {
+    diag_block<ST>(d, srcsel, blockIdx.x, gridDim.x, partials);
+}
+
+__global__ __launch_bounds__(kDiagThreads) void diag_final_kernel(
+    const double *__restrict__ partials, int blocks, double *__restrict__ out, double time) {
+    diag_final(partials, blocks, out, time);
+}
+
+// Every member of a batch in two launches (blockIdx.y: the member; each
+// reduces into its own simulation's partials exactly as it does alone).  Two
+// launches per member cost about 70 us each, most of it the serial final
+// sum: 31% of a 60-step pass of 48 members.
+template <int ST>
+__global__ __launch_bounds__(kDiagThreads) void diag_batch_kernel(
+    const InstDesc *__restrict__ descs, int first, int flip0, int flip1) {
+    const InstDesc d = descs[first + blockIdx.y];
+    const int blocks = diag_blocks((int64_t)d.nx * d.ny);
+    if ((int)blockIdx.x >= blocks) return;
+    diag_block<ST>(d, d.cur ^ (d.cls ? flip1 : flip0), blockIdx.x, blocks, d.partials);
+}
+
+__global__ __launch_bounds__(kDiagThreads) void diag_batch_final_kernel(
+    const InstDesc *__restrict__ descs, int first, double *__restrict__ out, int64_t steps) {
+    const int k = first + blockIdx.x;
+    const InstDesc d = descs[k];
+    diag_final(d.partials, diag_blocks((int64_t)d.nx * d.ny), out + (int64_t)k * TRT_NDIAG,
+               (double)(d.time0 + steps));
 }
 
 template <int ST>
@@ -296,15 +341,21 @@ __device__ void block_reduce_k(double v[K]) {
             for (int j = 0; j < K; ++j) v[j] = (MAX0 && j == 0) ? fmax(v[j], sh[k][j]) : v[j] + sh[k][j];
 }
 
+// The partials' sum in one workgroup, as diag_final (the maximum is of
+// magnitudes, so it starts from 0).
 template <int K, bool MAX0>
-__global__ void final_reduce_k(const double *__restrict__ partials, double *__restrict__ out) {
-    if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(kDiagThreads) void final_reduce_k(
+    const double *__restrict__ partials, int blocks, double *__restrict__ out) {
     double v[K];
-    for (int j = 0; j < K; ++j) v[j] = partials[j];
-    for (int b = 1; b < kDiagBlocks; ++b)
+#pragma unroll
+    for (int j = 0; j < K; ++j) v[j] = 0.0;
+    for (int b = threadIdx.x; b < blocks; b += kDiagThreads)
+#pragma unroll
         for (int j = 0; j < K; ++j)
             v[j] = (MAX0 && j == 0) ? fmax(v[j], partials[b * K + j]) : v[j] + partials[b * K + j];
-    for (int j = 0; j < K; ++j) out[j] = v[j];
+    block_reduce_k<K, MAX0>(v);
+    if (threadIdx.x == 0)
+        for (int j = 0; j < K; ++j) out[j] = v[j];
 }
 
 // Momentum exchange with solid nodes (Sec. III.D): every link from a fluid
@@ -320,14 +371,19 @@ __global__ __launch_bounds__(kDiagThreads) void wall_force_kernel(InstDesc d, in
     double v[2] = {0.0, 0.0};
     const int64_t n = (int64_t)d.nx * d.ny;
     if (d.mask != nullptr) {
+        // a node's link code names its solid pull sources: bit opp(i) is set
+        // where x + e_i is solid (or, in column 0 of an open lattice, beyond
+        // the inflow wall).  Reading it instead of nine mask bytes per node:
+        // 1050^2 FP64 31.9 -> 7 us.
+        const uint32_t skip0 = d.xbc ? ~((1u << 1) | (1u << 5) | (1u << 8)) : ~0u;
         for (int64_t k = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x; k < n;
-             k += (int64_t)kDiagBlocks * kDiagThreads) {
+             k += (int64_t)gridDim.x * kDiagThreads) {
             const int y = (int)(k / d.nx), x = (int)(k - (int64_t)y * d.nx);
-            if (d.mask[k]) continue;
+            uint32_t code = d.links[(int64_t)y * d.lpitch + x];
+            if (x == 0) code &= skip0;
+            if (code <= 1u || (code & 1u)) continue;
             for (int i = 1; i < 9; ++i) {
-                const int tx = x + kEx[i];
-                if (d.xbc && (tx < 0 || tx >= d.nx)) continue;
-                if (!is_solid(d.mask, d.nx, wrapi(tx, d.nx), wrapi(y + kEy[i], d.ny))) continue;
+                if (!((code >> kOpp[i]) & 1u)) continue;
                 const double fs = (double)b[i * d.plane + (int64_t)y * d.pitch + x] +
                                   (Store<ST>::shifted ? weight(i) : 0.0);
                 v[0] += 2.0 * kEx[i] * fs;
@@ -352,7 +408,7 @@ __global__ __launch_bounds__(kDiagThreads) void velocity_compare_kernel(
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     const int64_t n = (int64_t)d.nx * d.ny;
     for (int64_t k = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x; k < n;
-         k += (int64_t)kDiagBlocks * kDiagThreads) {
+         k += (int64_t)gridDim.x * kDiagThreads) {
         const int y = (int)(k / d.nx), x = (int)(k - (int64_t)y * d.nx);
         Moments<double, Store<ST>::shifted> m;
         if (node_moments<ST>(d, srcsel, x, y, m)) continue;
@@ -473,29 +529,50 @@ int diag_partial_count() { return kDiagBlocks; }
 
 hipError_t launch_diagnostics(const InstDesc &d, int storage, int src, double *partials,
                               double *out, double time, hipStream_t stream) {
-    TRT_DISPATCH(storage, (diag_kernel<S><<<kDiagBlocks, kDiagThreads, 0, stream>>>(d, src, partials)));
+    const int blocks = diag_blocks((int64_t)d.nx * d.ny);
+    TRT_DISPATCH(storage, (diag_kernel<S><<<blocks, kDiagThreads, 0, stream>>>(d, src, partials)));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    diag_final_kernel<<<1, 64, 0, stream>>>(partials, out, time);
+    diag_final_kernel<<<1, kDiagThreads, 0, stream>>>(partials, blocks, out, time);
     return hipGetLastError();
+}
+
+hipError_t launch_diagnostics_batch(const InstDesc *descs, int n, int64_t most_nodes, int storage,
+                                    int flip0, int flip1, int64_t steps, double *out,
+                                    hipStream_t stream) {
+    const int blocks = diag_blocks(most_nodes);
+    constexpr int kMembers = 32768;  // per launch: the grid's y extent
+    for (int first = 0; first < n; first += kMembers) {
+        const int m = n - first < kMembers ? n - first : kMembers;
+        TRT_DISPATCH(storage, (diag_batch_kernel<S><<<dim3(blocks, m), kDiagThreads, 0, stream>>>(
+                                  descs, first, flip0, flip1)));
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        diag_batch_final_kernel<<<m, kDiagThreads, 0, stream>>>(descs, first, out, steps);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_wall_force(const InstDesc &d, int storage, int src, double *partials,
                              double *out, hipStream_t stream) {
-    TRT_DISPATCH(storage, (wall_force_kernel<S><<<kDiagBlocks, kDiagThreads, 0, stream>>>(d, src, partials)));
+    const int blocks = diag_blocks((int64_t)d.nx * d.ny);
+    TRT_DISPATCH(storage, (wall_force_kernel<S><<<blocks, kDiagThreads, 0, stream>>>(d, src, partials)));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    final_reduce_k<2, false><<<1, 64, 0, stream>>>(partials, out);
+    final_reduce_k<2, false><<<1, kDiagThreads, 0, stream>>>(partials, blocks, out);
     return hipGetLastError();
 }
 
 hipError_t launch_velocity_compare(const InstDesc &d, int storage, int src, double *ref_ux,
                                    double *ref_uy, bool update, double *partials, double *out,
                                    hipStream_t stream) {
-    TRT_DISPATCH(storage, (velocity_compare_kernel<S><<<kDiagBlocks, kDiagThreads, 0, stream>>>(d, src, ref_ux, ref_uy, update ? 1 : 0, partials)));
+    const int blocks = diag_blocks((int64_t)d.nx * d.ny);
+    TRT_DISPATCH(storage, (velocity_compare_kernel<S><<<blocks, kDiagThreads, 0, stream>>>(d, src, ref_ux, ref_uy, update ? 1 : 0, partials)));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    final_reduce_k<4, true><<<1, 64, 0, stream>>>(partials, out);
+    final_reduce_k<4, true><<<1, kDiagThreads, 0, stream>>>(partials, blocks, out);
     return hipGetLastError();
 }
 

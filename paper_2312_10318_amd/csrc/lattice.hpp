@@ -94,8 +94,12 @@ struct InstDesc {
     // (u_in, 0) at density rho_in, pressure outlet at x = nx - 1 held at
     // rho_out; xbc = 0: periodic in x
     int32_t xbc;
-    int32_t pad2_;
+    // in a batch's table: the member's class (1: it takes launches of several
+    // steps) and its time when the table was built
+    int32_t cls;
+    int64_t time0;
     double u_in, rho_in, rho_out;
+    double *partials;     // the simulation's reduction partials (null: none of its own)
 };
 
 // Products w_i * X.  In FP32 the rounded weights fl(4/9), fl(1/9), fl(1/36)
