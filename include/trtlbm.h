@@ -90,8 +90,8 @@ typedef enum {
  *    He's pressure rule; populations leaving through x = nx are lost;
  *  - the gradient of Phi = rho u^3 sees rho_in u_in^3 beyond the inflow
  *    wall and the last column's value beyond the outlet.
- * Neither rule includes the body force.  Open-boundary lattices run the
- * sweep with the link map (one or two columns per lane). */
+ * Neither rule includes the body force.  Open-boundary lattices run with the
+ * link map. */
 typedef struct {
     int32_t nx, ny;        /* lattice size, 1..46340 each; periodic in y (and x unless open) */
     double tau_s;          /* tau_s1 > 1/2: viscosity nu = (tau_s - 1/2)/3 (Sec. II.C) */
@@ -115,7 +115,18 @@ typedef struct {
  * paired access per population) applies to lattices of at most 4 GiB whose
  * width is not 1 mod 128, with or without a mask or open boundaries;
  * elsewhere the sweep uses one column per lane whatever is asked.  The two
- * shapes compute the same arithmetic per node. */
+ * shapes compute the same arithmetic per node.
+ *
+ * Where rows_per_wave, waves_per_block, cols_per_lane, steps_per_sweep and
+ * prefetch_rows are all zero, lattices of at least 16 rows may also take a
+ * pass of two or three time steps per launch with one column per lane, which
+ * applies to every storage, mask and boundary within 4 GiB: FP64 lattices,
+ * lattices with a mask that does not fill whole rows or with open x
+ * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1100^2 nodes.
+ * trt_get_tuning then reports that pass's rows, wavefronts, steps and
+ * prefetch (cols_per_lane stays the one-step sweeps').  Setting any of these
+ * fields asks for the passes they describe.  Every choice gives the same
+ * bits. */
 typedef struct {
     int32_t rows_per_wave;   /* rows one wavefront marches through, 1..4096 (0: automatic) */
     int32_t waves_per_block; /* wavefronts per workgroup: 1, 2, 4, 8 or 16 (0: automatic); the
@@ -145,13 +156,13 @@ typedef struct {
     int32_t steps_per_sweep; /* time steps per launch: 1, 2 or 3 (0: automatic -- three for
                                 FP32 simulations of at least 2048^2 nodes that allow it, else
                                 two where allowed; in a batch three for FP32 members, two for
-                                FP16).  k steps per launch move each
+                                FP16; and see above).  k steps per launch move each
                                 population through HBM once per k steps and give the bits of
                                 k one-step sweeps.  Two apply to FP32 and FP16 simulations,
                                 alone or in a batch, without a mask or open boundaries, or
                                 with a mask whose solid nodes fill whole rows (x periodic);
                                 three to such FP32 simulations, alone or in an FP32 batch;
-                                elsewhere sweeps take fewer steps.  With
+                                elsewhere a request for more gives one.  With
                                 two or three steps per launch, rows_per_wave and
                                 waves_per_block shape that pass (cols_per_lane the one-step
                                 sweeps of leftover steps). */

@@ -107,6 +107,10 @@ def save_cache(cache: dict, path: str | None = None) -> bool:
     return True
 
 
+# every field automatic (XCD remap -1: the pass's default)
+AUTOMATIC = (0, 0, -1, 0, 0, 0, 0)
+
+
 def candidates(nx: int, ny: int, has_mask: bool = False, storage: str = "f32",
                walls: bool = False):
     """Launch shapes (rows, waves per workgroup, XCD remap, columns per
@@ -190,7 +194,9 @@ def tune(nx: int, ny: int, storage: str = "f32", mask=None, steps: int | None = 
     if steps is None:
         steps = max(10, min(400, int(2e9 / max(1, nx * ny))))
     table = []
-    for shape in shapes or candidates(nx, ny, mask is not None, storage, row_walls(mask)):
+    # the library's own choice too: some of its passes take no shape
+    for shape in shapes or [AUTOMATIC] + candidates(nx, ny, mask is not None, storage,
+                                                    row_walls(mask)):
         ms = time_shape(lat, shape, steps, max(2, steps // 10))
         table.append((list(shape), ms))
         if log:

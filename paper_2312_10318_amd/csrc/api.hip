@@ -185,6 +185,7 @@ struct trt_sim {
     hipStream_t stream;
     InstDesc desc;  // desc.cur stays 0: the lattice read is passed per launch
     Launch launch;
+    trt::NarrowPlan narrow;  // one column per lane, several steps per launch (k = 0: not taken)
     int cur;        // lattice holding the current state
     int64_t time;
     double *scratch;  // diagnostics partials + one TRT_NDIAG result
@@ -324,6 +325,7 @@ template <class F> trt_status capture(hipStream_t cap, hipGraphExec_t &out, F bo
 // memory-side cache.
 constexpr int64_t kTb3MinNodes = 2048LL * 2048LL;
 int sim_k(const trt_sim *s) {
+    if (s->narrow.k) return s->narrow.k;
     const int want = s->launch.steps_per_sweep;
     const int st = s->prob.storage;
     if (trt::tb3_eligible(s->desc, st) &&
@@ -336,6 +338,11 @@ int sim_k(const trt_sim *s) {
 // One launch of k time steps (k as sim_k or lower) reading lattice src.
 hipError_t sim_launch(const trt_sim *s, int k, int src, hipStream_t stream) {
     const int st = s->prob.storage;
+    if (s->narrow.k && k > 1) {
+        trt::NarrowPlan p = s->narrow;
+        p.k = k;
+        return trt::launch_narrow(s->desc, st, p, src, stream);
+    }
     if (k == 3) return trt::launch_sweep_tb3(s->desc, st, src, s->launch, stream);
     if (k == 2) return trt::launch_sweep_tb2(s->desc, st, src, s->launch, stream);
     return trt::launch_sweep(s->desc, st, s->prob.mask != nullptr, src, s->launch, stream);
@@ -545,6 +552,7 @@ trt_status trt_create(const trt_problem *p, void *f_a, void *f_b, void *hip_stre
         }
     }
     trt::tile(d, s->launch, p->storage);
+    s->narrow = trt::narrow_plan(d, p->storage, s->launch);
     // the capture stream is created at the first capture (batch members never
     // capture their own step)
     *out = s;
@@ -559,6 +567,7 @@ trt_status trt_set_tuning(trt_sim *s, const trt_tuning *t) {
     if (s->in_batch) return fail(TRT_ESTATE, "simulation is a batch member");
     s->launch = l;
     trt::tile(s->desc, l, s->prob.storage);
+    s->narrow = trt::narrow_plan(s->desc, s->prob.storage, l);
     release_graphs(s->graphs);
     return TRT_OK;
 }
@@ -567,6 +576,18 @@ trt_status trt_get_tuning(const trt_sim *s, trt_tuning *t) {
     if (check_sim(s) != TRT_OK) return TRT_EINVAL;
     if (!t) return fail(TRT_EINVAL, "out is NULL");
     const int ks = sim_k(s);
+    t->cols_per_lane = s->desc.cols;
+    t->batch_items = 0;
+    t->batch_order = 0;
+    t->graph_steps = s->launch.graph_steps;
+    t->steps_per_sweep = ks;
+    if (s->narrow.k) {
+        t->rows_per_wave = s->narrow.rows;
+        t->waves_per_block = s->narrow.waves_per_block;
+        t->xcd_remap = s->narrow.remap;
+        t->prefetch_rows = 1;
+        return TRT_OK;
+    }
     t->rows_per_wave = ks == 3   ? trt::tb3_desc(s->desc, s->launch).rows
                        : ks == 2 ? trt::tb2_desc(s->desc, s->launch).rows
                                  : s->desc.rows;
@@ -575,11 +596,6 @@ trt_status trt_get_tuning(const trt_sim *s, trt_tuning *t) {
         : ks == 2 ? trt::tb2_waves_per_block(s->desc, s->prob.storage, s->launch)
                   : trt::single_waves_per_block(s->desc, s->prob.storage, s->launch);
     t->xcd_remap = ks == 3 ? trt::tb3_xcd_remap(s->desc, s->launch) : s->launch.xcd_remap;
-    t->cols_per_lane = s->desc.cols;
-    t->batch_items = 0;
-    t->batch_order = 0;
-    t->graph_steps = s->launch.graph_steps;
-    t->steps_per_sweep = ks;
     t->prefetch_rows = ks == 3   ? trt::tb3_prefetch_rows(s->desc, s->launch)
                        : ks == 2 ? trt::tb2_prefetch_rows(s->desc, s->prob.storage, s->launch)
                                  : 0;

@@ -165,6 +165,23 @@ hipError_t launch_sweep_tb3_batch(const InstDesc *descs, int ndescs, const int4 
                                   int nitems, int storage, int flip, const Launch &l,
                                   hipStream_t stream);
 
+// Several time steps per launch with one column per lane (narrow.hip): any
+// storage, mask and boundary, k = 2, or 3 with FP32 or FP16 storage.  A
+// wavefront's window of 64 columns stores narrow_valid(k) of them.
+constexpr int narrow_valid(int k) { return 64 - 2 * (2 * k - 1); }
+// fewer rows than this run fewer than a block's own rows of fill
+constexpr int kNarrowMinRows = 16;
+bool narrow_eligible(const InstDesc &d, int storage);
+// The launch shape under which a lattice takes the pass; k = 0: it does not.
+struct NarrowPlan {
+    int k, rows, waves_per_block, remap;
+};
+NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l);
+// The instance tiled for the pass.
+InstDesc narrow_desc(const InstDesc &d, int k, int rows);
+hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, int src,
+                         hipStream_t stream);
+
 // The access-pattern probe (a measurement aid): one launch moves the lattice
 // `src` to the other one with the two-column sweep's loads, stores, launch
 // shape and barriers and none of its arithmetic.  Only for two-column

@@ -1,0 +1,547 @@
+// narrow.hip -- several time steps per launch with one column per lane.
+//
+// A wavefront computes a window of 64 columns, one per lane, and marches it
+// up a row block as the row pipeline of the 128-column passes does: every
+// pipeline row gathers one row of the stored state, and each step's collided
+// populations stay in registers until the next step has pulled them.  Half
+// the columns per wavefront means half the instructions per pipeline row and
+// twice the wavefronts, which is what lattices too small to fill the 1024
+// SIMDs with 128-column windows need; and a third of the registers of a
+// column pair, which is what makes two steps per launch possible in FP64.
+//
+// With LINK the lattice may have any mask and open x boundaries: a node's
+// link code (InstDesc::links) says which of its pulls come back from its own
+// slots.  In the first step a lane picks the address it loads from; in later
+// steps it picks between the neighbour's value and its own, whose populations
+// the window keeps.  Rows whose link summary is 0 for the window skip both.
+//
+// The first step's pulls are exact in all 64 lanes (each lane loads its own
+// neighbours' elements); its gradient of Phi_x then spoils one lane on
+// each side, and every later step two more (its pull and its gradient), so a
+// window of K steps stores its middle 64 - 2 (2 K - 1) columns.  A row block
+// of R rows gathers R + 2 (2 K - 1) rows.  Every node's arithmetic is the
+// one-step sweep's, on the values that sweep would store and load back, so K
+// steps per launch give its bits.
+#include <type_traits>
+
+#include "wave.hpp"
+
+namespace trt {
+
+namespace {
+
+// A collided population between two steps: FP16 holds the stored half.
+template <int ST> struct Pop {
+    using W = typename Store<ST>::C;
+    __device__ static __forceinline__ W widen(W v) { return v; }
+    __device__ static __forceinline__ W shr(W v) { return dpp_shr(W(0), v); }
+    __device__ static __forceinline__ W shl(W v) { return dpp_shl(W(0), v); }
+};
+template <> struct Pop<ST_F16> {
+    using W = uint32_t;
+    __device__ static __forceinline__ float widen(W v) {
+        return (float)__builtin_bit_cast(_Float16, (unsigned short)(v & 0xffffu));
+    }
+    __device__ static __forceinline__ W shr(W v) { return dpp_shr(0u, v); }
+    __device__ static __forceinline__ W shl(W v) { return dpp_shl(0u, v); }
+};
+
+// One step's collided rows in flight: the row behind the fresh one (all nine
+// populations with LINK, whose nodes may take their own back; else 0, 1, 3 and
+// those streaming up, 2, 5, 6) and, of the row behind that, 2, 5, 6.
+template <int ST, bool LINK> struct Window {
+    using W = typename Pop<ST>::W;
+    W lo[3];
+    W mid[LINK ? 9 : 6];
+};
+// where population i sits in Window::mid (-1: not kept)
+template <bool LINK> __host__ __device__ constexpr int mid_of(int i) {
+    constexpr int at[9] = {0, 1, 3, 2, -1, 4, 5, -1, -1};
+    return LINK ? i : at[i];
+}
+
+template <int ST, int K, bool LINK> struct NarrowState {
+    using C = typename Store<ST>::C;
+    Coeffs<C> k[K];        // per step: the next row to collide,
+    C py[K], below[K];     // its Phi_y and that of the row below it
+    Window<ST, LINK> w[K - 1];
+    uint32_t code[K];      // LINK: half j of the whole: the code of row y + 2 K - 1 - j
+    uint32_t flagged;      // LINK (uniform): bit j: that row has links in the window
+};
+
+template <int ST, bool LINK> struct NarrowRow {
+    typename Store<ST>::T v[9];
+    uint32_t code;
+    uint32_t flagged;
+};
+
+// The collision's constants.
+template <class C> struct Consts {
+    C w1, w2, ph, gx, gy;
+    __device__ __forceinline__ explicit Consts(const InstDesc &d)
+        : w1(uniform((C)d.omega1)), w2(uniform((C)d.omega2)), ph(uniform((C)d.phi)),
+          gx(uniform((C)d.gx)), gy(uniform((C)d.gy)) {}
+};
+
+// What a wavefront needs of its lattice.
+template <int ST, bool LINK> struct NarrowCtx {
+    using T = typename Store<ST>::T;
+    using C = typename Store<ST>::C;
+    BufAccess<T> in, out;
+    LinkAccess la;
+    Column col;
+    int64_t plane;
+    int pitch, ny, nx;
+    int64_t lpitch;
+    const __attribute__((address_space(4))) uint32_t *sum;
+    int nsum, s0, s1, s2;  // the summary entries that cover the window
+    bool bounds;           // (uniform) the window holds a boundary column of open x
+    bool store;
+    OpenX<C> ox;
+
+    __device__ __forceinline__ uint32_t summary(int y) const {
+        if constexpr (!LINK) return 0u;
+        const int64_t r = (int64_t)y * nsum;
+        return sum[r + s0] | sum[r + s1] | sum[r + s2];
+    }
+    // the codes of row y's nodes (0 where the row has no links)
+    __device__ __forceinline__ uint32_t codes(int y, uint32_t flagged) const {
+        if constexpr (!LINK) return 0u;
+        return flagged ? la.ld1((uint32_t)((int64_t)y * lpitch), (uint32_t)col.xc) : 0u;
+    }
+};
+
+// Load the pulls of row y (row.code, row.flagged already hold the row's).
+template <int ST, bool LINK>
+__device__ __forceinline__ void narrow_load(NarrowRow<ST, LINK> &row,
+                                            const NarrowCtx<ST, LINK> &c, int y) {
+    using T = typename Store<ST>::T;
+    constexpr uint32_t es = sizeof(T);
+    const int ym = (y == 0) ? c.ny - 1 : y - 1;
+    const int yp = (y == c.ny - 1) ? 0 : y + 1;
+    const int64_t e0 = (int64_t)y * c.pitch, em = (int64_t)ym * c.pitch,
+                  ep = (int64_t)yp * c.pitch;
+    const int64_t from[9] = {e0,
+                             c.plane + e0,
+                             2 * c.plane + em,
+                             3 * c.plane + e0,
+                             4 * c.plane + ep,
+                             5 * c.plane + em,
+                             6 * c.plane + em,
+                             7 * c.plane + ep,
+                             8 * c.plane + ep};
+    const uint32_t oc = c.col.oc, om = c.col.om, op = c.col.op;
+    const uint32_t at[9] = {oc, om, oc, op, oc, om, op, op, om};
+    if constexpr (!LINK) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ld(from[i], at[i]);
+    } else {
+        // whole byte offsets (the lattice is at most 4 GiB), so that a lane
+        // can point at its own slot instead
+        uint32_t off[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) off[i] = at[i] + (uint32_t)(from[i] * es);
+        if (row.flagged) {
+#pragma unroll
+            for (int i = 1; i < 9; ++i) {
+                const uint32_t own = oc + (uint32_t)((kOppDir[i] * c.plane + e0) * es);
+                off[i] = ((row.code >> i) & 1u) ? own : off[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ld(0, off[i]);
+    }
+}
+
+// Moments, gradient of Phi_x and coefficients of a row from its nodes'
+// populations; returns Phi_y.
+template <int ST, bool LINK>
+__device__ __forceinline__ typename Store<ST>::C narrow_coeffs(
+    Coeffs<typename Store<ST>::C> &k, typename Store<ST>::C f[9], uint32_t code,
+    const NarrowCtx<ST, LINK> &c, const Consts<typename Store<ST>::C> &rt) {
+    using C = typename Store<ST>::C;
+    constexpr bool SH = Store<ST>::shifted;
+    if (LINK && c.bounds)
+        open_x_fix<C, SH>(f, c.col.xc, c.nx, c.ox.u_in, c.ox.rho_in, c.ox.rho_out);
+    Moments<C, SH> m;
+    m.compute(f, rt.gx, rt.gy);
+    const bool solid = LINK && (code & 1u);
+    const C px = m.rho * m.ux * m.ux * m.ux;
+    const C py = m.rho * m.uy * m.uy * m.uy;
+    const C phix = solid ? C(0) : px;
+    C left = dpp_shr(C(0), phix), right = dpp_shl(C(0), phix);
+    if (LINK && c.bounds) {
+        // Phi beyond the inflow wall is the wall's; beyond the outlet, the
+        // last column's
+        if (c.col.xc == 0) left = c.ox.phi_wall;
+        if (c.col.xc == c.nx - 1) right = phix;
+    }
+    k = collide_coeffs<C, SH>(m, C(0.5) * (right - left), rt.w1, rt.w2, rt.ph, rt.gx, rt.gy);
+    return solid ? C(0) : py;
+}
+
+// The collided populations of a row as the one-step sweep stores them.
+template <int ST>
+__device__ __forceinline__ void narrow_collide(typename Pop<ST>::W o[9],
+                                               const Coeffs<typename Store<ST>::C> &k,
+                                               typename Store<ST>::C dphiy,  // above - below
+                                               const Consts<typename Store<ST>::C> &rt) {
+    using C = typename Store<ST>::C;
+    const C dpy = C(0.5) * dphiy;
+    if constexpr (ST == ST_F16) {
+        HalfPairs p;
+        reconstruct_pairs(p, k.base, k.bx, k.by, k.bxx, k.byy - rt.ph * dpy, k.bxy, k.bxxy,
+                          k.bxyy);
+        o[0] = half_out<0, false>(p);
+        o[1] = half_out<1, false>(p);
+        o[2] = half_out<2, false>(p);
+        o[3] = half_out<3, false>(p);
+        o[4] = half_out<4, false>(p);
+        o[5] = half_out<5, false>(p);
+        o[6] = half_out<6, false>(p);
+        o[7] = half_out<7, false>(p);
+        o[8] = half_out<8, false>(p);
+    } else {
+        reconstruct<C>(o, k.base, k.bx, k.by, k.bxx, k.byy - rt.ph * dpy, k.bxy, k.bxxy, k.bxyy);
+    }
+}
+
+template <int ST>
+__device__ __forceinline__ typename Store<ST>::T narrow_out(typename Pop<ST>::W v) {
+    if constexpr (ST == ST_F16)
+        return __builtin_bit_cast(_Float16, (unsigned short)(v & 0xffffu));
+    else
+        return v;
+}
+
+// Step Q + 1 of pipeline row y: its row behind the fresh one (whose
+// coefficients and Phi_y the caller has just formed) collides; then the
+// next step pulls the row behind that one and forms its coefficients, or, in
+// the last step, the row is stored.  FILL: stage g < 2 K - 1 of the pipeline's
+// fill runs the first g of these collisions and pulls.
+template <int Q, int ST, int K, bool LINK, bool FILL>
+__device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
+                                            const Coeffs<typename Store<ST>::C> &fresh_k,
+                                            typename Store<ST>::C fresh_y,
+                                            const NarrowCtx<ST, LINK> &c,
+                                            const Consts<typename Store<ST>::C> &rt, int y,
+                                            int stage) {
+    using C = typename Store<ST>::C;
+    using P = Pop<ST>;
+    using W = typename P::W;
+    W o[9];
+    if (!FILL || stage > 2 * Q) narrow_collide<ST>(o, s.k[Q], fresh_y - s.below[Q], rt);
+    s.below[Q] = s.py[Q];
+    s.py[Q] = fresh_y;
+    s.k[Q] = fresh_k;
+    if (FILL && stage <= 2 * Q) return;
+    if constexpr (Q == K - 1) {
+        // row y of the last step: a solid node keeps zeros (its slots are
+        // never read)
+        if constexpr (LINK) {
+            if ((s.flagged >> (2 * K - 1)) & 1u) {
+                const bool solid = (s.code[K - 1] >> 16) & 1u;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) o[i] = solid ? W(0) : o[i];
+            }
+        }
+        if (c.store) {
+            const int64_t e0 = (int64_t)y * c.pitch;
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                c.out.st(i * c.plane + e0, c.col.oc, narrow_out<ST>(o[i]));
+        }
+    } else {
+        Window<ST, LINK> &w = s.w[Q];
+        constexpr auto at = mid_of<LINK>;
+        Coeffs<C> next_k;
+        C next_y = C(0);
+        if (!FILL || stage > 2 * Q + 1) {
+            W g[9];
+            g[0] = w.mid[at(0)];
+            g[1] = P::shr(w.mid[at(1)]);
+            g[3] = P::shl(w.mid[at(3)]);
+            g[2] = w.lo[0];
+            g[5] = P::shr(w.lo[1]);
+            g[6] = P::shl(w.lo[2]);
+            g[4] = o[4];
+            g[7] = P::shl(o[7]);
+            g[8] = P::shr(o[8]);
+            uint32_t code = 0u;
+            if constexpr (LINK) {
+                if ((s.flagged >> (2 * Q + 2)) & 1u) {
+                    code = s.code[Q + 1] & 0xffffu;
+#pragma unroll
+                    for (int i = 1; i < 9; ++i)
+                        g[i] = ((code >> i) & 1u) ? w.mid[at(kOppDir[i])] : g[i];
+                }
+            }
+            C f[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) f[i] = P::widen(g[i]);
+            next_y = narrow_coeffs<ST, LINK>(next_k, f, code, c, rt);
+        }
+        w.lo[0] = w.mid[at(2)];
+        w.lo[1] = w.mid[at(5)];
+        w.lo[2] = w.mid[at(6)];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            if (at(i) >= 0) w.mid[at(i)] = o[i];
+        if (!FILL || stage > 2 * Q + 1)
+            narrow_step<Q + 1, ST, K, LINK, FILL>(s, next_k, next_y, c, rt, y, stage);
+    }
+}
+
+// One pipeline row y: the first step's coefficients of gathered row
+// y + 2 K - 1, whose registers then take the loads of row yload (when
+// `load`), and the later parts (narrow_step).
+template <int ST, int K, bool LINK, bool FILL>
+__device__ __forceinline__ void narrow_row(NarrowState<ST, K, LINK> &s, NarrowRow<ST, LINK> &row,
+                                           const NarrowCtx<ST, LINK> &c,
+                                           const Consts<typename Store<ST>::C> &rt, int y,
+                                           bool load, int yload, uint32_t &next_flag,
+                                           uint32_t &next_code, int stage) {
+    using C = typename Store<ST>::C;
+    Coeffs<C> k;
+    uint32_t code = 0u;
+    C f[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) f[i] = to_c(row.v[i]);
+    if constexpr (LINK) {
+        code = row.code;
+        s.flagged = (s.flagged << 1) | (row.flagged ? 1u : 0u);
+#pragma unroll
+        for (int j = K - 1; j > 0; --j) s.code[j] = (s.code[j] << 16) | (s.code[j - 1] >> 16);
+        s.code[0] = (s.code[0] << 16) | code;
+    }
+    if (load) {
+        if constexpr (LINK) {
+            // the codes of the row after this one go out ahead of this row's
+            // populations, which are waited for first
+            row.code = next_code;
+            row.flagged = next_flag;
+            const int y1 = (yload + 1 == c.ny) ? 0 : yload + 1;
+            next_flag = c.summary(y1);
+            next_code = c.codes(y1, next_flag);
+        }
+        narrow_load<ST, LINK>(row, c, yload);
+    }
+    const C py = narrow_coeffs<ST, LINK>(k, f, code, c, rt);
+    narrow_step<0, ST, K, LINK, FILL>(s, k, py, c, rt, y, stage);
+}
+
+// One window through one row block.
+template <int ST, int K, bool LINK>
+__device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int rb, int srcsel) {
+    using T = typename Store<ST>::T;
+    using C = typename Store<ST>::C;
+    constexpr int edge = 2 * K - 1;  // lanes (and rows) lost on each side
+    const int lane = threadIdx.x & 63;
+    const int nx = d.nx, ny = d.ny;
+    const T *__restrict__ src = static_cast<const T *>(srcsel ? d.buf[1] : d.buf[0]);
+    T *__restrict__ dst = static_cast<T *>(srcsel ? d.buf[0] : d.buf[1]);
+    const uint64_t bytes = (uint64_t)ny * (uint64_t)d.pitch * sizeof(T);
+    const int x0 = strip * narrow_valid(K) - edge;  // lane 0's column before wrapping
+    const Column col = column_of(x0 + lane, nx, sizeof(T));
+    const bool store = lane >= edge && lane < 64 - edge && x0 + lane < nx;
+    const Consts<C> rt(d);
+    OpenX<C> ox;
+    ox.on = LINK && d.xbc != 0;
+    ox.nx = nx;
+    ox.u_in = (C)d.u_in;
+    ox.rho_in = (C)d.rho_in;
+    ox.rho_out = (C)d.rho_out;
+    ox.phi_wall = ox.rho_in * ox.u_in * ox.u_in * ox.u_in;
+    const bool bounds =
+        LINK && ox.on && __builtin_amdgcn_ballot_w64(col.xc == 0 || col.xc == nx - 1) != 0;
+    // the summary entries (64 columns each) that cover the window: its first
+    // lane's, the one after it or the lattice's last, and the first after a wrap
+    int s0 = 0, s1 = 0, s2 = 0;
+    if (LINK && nx > 64) {
+        int a = x0 % nx;
+        if (a < 0) a += nx;
+        const int b = min(a + 63, nx - 1);
+        s0 = a >> 6;
+        s1 = b >> 6;
+        s2 = a + 63 >= nx ? 0 : s0;
+    }
+    const NarrowCtx<ST, LINK> c{BufAccess<T>(src, bytes),
+                                BufAccess<T>(dst, bytes),
+                                LinkAccess(d.links, (uint64_t)ny * (uint64_t)d.lpitch),
+                                col,
+                                d.plane,
+                                d.pitch,
+                                ny,
+                                nx,
+                                d.lpitch,
+                                (const __attribute__((address_space(4))) uint32_t *)d.rowsum,
+                                d.nsum,
+                                s0,
+                                s1,
+                                s2,
+                                bounds,
+                                store,
+                                ox};
+    const int y0 = rb * d.rows;
+    const int y1 = min(y0 + d.rows, ny);
+    const auto wrap_row = [&](int v) { v %= ny; return v < 0 ? v + ny : v; };
+
+    NarrowState<ST, K, LINK> s{};
+    NarrowRow<ST, LINK> row;
+    // the first gathered row, y0 - edge, and the codes of the row after it
+    const int first = wrap_row(y0 - edge), second = wrap_row(y0 - edge + 1);
+    row.flagged = c.summary(first);
+    row.code = c.codes(first, row.flagged);
+    uint32_t next_flag = c.summary(second), next_code = c.codes(second, next_flag);
+    narrow_load<ST, LINK>(row, c, first);
+    int y = y0 - 2 * edge;
+    int yl = second;  // the row to load next, y + 2 K wrapped
+    for (int i = 0; i < 2 * edge; ++i, ++y) {
+        narrow_row<ST, K, LINK, true>(s, row, c, rt, y, y + 2 * K <= y1 + edge - 1, yl, next_flag,
+                                      next_code, i >> 1);
+        yl = yl + 1 == ny ? 0 : yl + 1;
+    }
+    for (; y < y1; ++y) {
+        narrow_row<ST, K, LINK, false>(s, row, c, rt, y, y + 2 * K <= y1 + edge - 1, yl,
+                                       next_flag, next_code, 2 * K);
+        yl = yl + 1 == ny ? 0 : yl + 1;
+    }
+}
+
+constexpr int kNarrowMaxWaves = 4;
+
+template <int ST, int K, bool LINK>
+__global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(InstDesc d, int srcsel,
+                                                                     int remap) {
+    int b = blockIdx.x;
+    if (remap) b = xcd_remap(b, gridDim.x);
+    const int wpb = blockDim.x >> 6;
+    const int wave = b * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= d.strips * d.rowblocks) return;
+    const int rb = wave / d.strips;
+    narrow_strip<ST, K, LINK>(d, wave - rb * d.strips, rb, srcsel);
+}
+
+// Batched: wavefront w takes item w = (member, window, row block, -).
+template <int ST, int K, bool LINK>
+__global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_batch_kernel(
+    const InstDesc *__restrict__ descs, int ndescs, const int4 *__restrict__ items, int nitems,
+    int flip, int remap) {
+    int b = blockIdx.x;
+    if (remap) b = xcd_remap(b, gridDim.x);
+    const int wpb = blockDim.x >> 6;
+    const int wave = b * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= nitems) return;
+    const int4 it = items[wave];
+    if ((unsigned)it.x >= (unsigned)ndescs) return;
+    const InstDesc d = descs[it.x];
+    narrow_strip<ST, K, LINK>(d, it.y, it.z, d.cur ^ flip);
+}
+
+template <int ST, int K>
+hipError_t launch_narrow_t(const InstDesc &t, int src, int wpb, int remap, hipStream_t s) {
+    const int waves = t.strips * t.rowblocks;
+    const int blocks = (waves + wpb - 1) / wpb;
+    if (t.links)
+        narrow_kernel<ST, K, true><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+    else
+        narrow_kernel<ST, K, false><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+    return hipGetLastError();
+}
+
+template <int ST>
+hipError_t launch_narrow_k(const InstDesc &t, int k, int src, int wpb, int remap, hipStream_t s) {
+    if (k == 2) return launch_narrow_t<ST, 2>(t, src, wpb, remap, s);
+    if constexpr (ST != ST_F64)
+        if (k == 3) return launch_narrow_t<ST, 3>(t, src, wpb, remap, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool narrow_eligible(const InstDesc &d, int storage) {
+    const bool general = d.mask != nullptr || d.xbc != 0;
+    return d.ny >= kNarrowMinRows && buffer_addressable(d, storage) &&
+           (!general || d.links != nullptr);
+}
+
+InstDesc narrow_desc(const InstDesc &d, int k, int rows) {
+    InstDesc t = d;
+    t.strips = (d.nx + narrow_valid(k) - 1) / narrow_valid(k);
+    t.rows = rows;
+    t.rowblocks = (d.ny + rows - 1) / rows;
+    return t;
+}
+
+hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, int src,
+                         hipStream_t stream) {
+    if (!narrow_eligible(d, storage)) return hipErrorInvalidValue;
+    const InstDesc t = narrow_desc(d, p.k, p.rows);
+    switch (storage) {
+        case ST_F64: return launch_narrow_k<ST_F64>(t, p.k, src, p.waves_per_block, p.remap, stream);
+        case ST_F32: return launch_narrow_k<ST_F32>(t, p.k, src, p.waves_per_block, p.remap, stream);
+        case ST_F16: return launch_narrow_k<ST_F16>(t, p.k, src, p.waves_per_block, p.remap, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// Which lattices take the pass, how many steps per launch and with what rows.
+// Only where every field of the launch shape is automatic: a caller that
+// sets one asks for the passes those fields describe.  Measured on one box, us
+// per step, the other passes' default against this one's best shape and,
+// where it differs, the shape chosen here:
+//   FP64 (two steps; one per launch before): 128^2 6.6 / 3.1, 256^2 7.6 / 3.7,
+//     512^2 13.0 / 6.0, 1024^2 33.5 / 18.0, 2048^2 112 / 70, 4096^2 408 / 271;
+//     cylinder 400 x 200 14.5 / 5.7, 1050^2 43.8 / 20.4; channel 1000^2
+//     32.2 / 18.2.
+//   FP32, any link map but whole-row walls (one step before): cylinder
+//     400 x 200 two steps 4.7, three 5.5 against 12.6; 1050^2 13.5 / 12.6
+//     against 26.4; obstacle 2048^2 38.0 / 31.2 against 68.6 -- three steps
+//     pay once the lattice leaves the L2s.
+//   FP32, open or whole-row walls (128-column windows before): 128^2 8.0 / 2.6,
+//     256^2 8.0 / 3.1, 512^2 8.6 / 4.2, 724^2 9.1 / 6.0, 1024^2 12.6 / 10.6
+//     (three steps 8.2 there, but callers rely on two and eight rows as the
+//     default at that size), 1448^2 19.6 / 15.5 (three steps; two 20.1),
+//     2048^2 27.9 / 27.3; channel 1001 x 513 10.5 / 7.1.
+//   FP16: 128^2 7.5 / 3.2, 512^2 8.2 / 5.3, 1024^2 11.9 / 9.9, 2048^2 25.9 /
+//     27.3 (so not there); cylinder 1050^2 21.1 / 12.8; obstacle 2048^2 47.4 /
+//     34.7 (three steps 35.2).
+// Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows, so R is the
+// smallest that leaves at most two wavefronts per SIMD (FP64: one) -- up to a
+// cap from where the launch is bound by memory rather than by latency and
+// shorter blocks in more rounds balance better (FP64 2048^2: 8 rows 70, 12
+// rows 71.5, 16 and up over 73 us; 182 VGPRs with links keep two wavefronts
+// per SIMD, 1050^2: 8 rows 26.3, 10 rows 20.4).
+NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
+    NarrowPlan p = {0, 0, 0, 0};
+    const bool automatic = l.rows_per_wave == 0 && l.waves_per_block == 0 && l.cols_per_lane == 0 &&
+                           l.steps_per_sweep == 0 && l.prefetch_rows == 0;
+    if (!automatic || !narrow_eligible(d, storage)) return p;
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    const bool wide = tb2_eligible(d, storage);  // the 128-column passes apply
+    constexpr int64_t k1 = 1024;
+    int cap;
+    if (storage == ST_F64) {
+        p.k = 2;
+        cap = d.links ? 10 : 8;
+    } else if (storage == ST_F32) {
+        if (wide && nodes >= 2048 * 2048) return p;
+        p.k = nodes > (wide ? k1 * k1 : k1 * k1 / 2) ? 3 : 2;
+        cap = p.k == 2 ? 8 : 16;
+    } else {
+        if (wide && nodes > k1 * k1 * 5 / 4) return p;
+        p.k = 2;
+        cap = nodes > k1 * k1 * 5 / 4 ? 24 : 6;
+    }
+    const int64_t strips = (d.nx + narrow_valid(p.k) - 1) / narrow_valid(p.k);
+    const auto waves = [&](int r) { return strips * ((d.ny + r - 1) / r); };
+    const int64_t most = storage == ST_F64 ? 1024 : 2048;
+    // a single row per block only while that leaves one wavefront per SIMD
+    p.rows = waves(1) <= 1024 ? 1 : 2;
+    while (p.rows < cap && waves(p.rows) > most) ++p.rows;
+    p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
+    p.remap = l.remap_asked ? l.xcd_remap : 1;
+    return p;
+}
+
+}  // namespace trt

@@ -29,31 +29,13 @@
 // contributes Phi = 0.
 #include <type_traits>
 
-#include "kernels.hpp"
+#include "wave.hpp"
 
 namespace trt {
 
 
 namespace {
 
-
-// Per-lane geometry of one strip column.
-struct Column {
-    int xm, xc, xp;        // wrapped columns x-1, x, x+1
-    uint32_t om, oc, op;   // their byte offsets within a row
-};
-
-__device__ __forceinline__ Column column_of(int c, int nx, uint32_t elem) {
-    Column col;
-    col.xc = c % nx;
-    if (col.xc < 0) col.xc += nx;
-    col.xm = (col.xc == 0) ? nx - 1 : col.xc - 1;
-    col.xp = (col.xc == nx - 1) ? 0 : col.xc + 1;
-    col.om = (uint32_t)col.xm * elem;
-    col.oc = (uint32_t)col.xc * elem;
-    col.op = (uint32_t)col.xp * elem;
-    return col;
-}
 
 // Raw (storage-precision) populations of one node, gathered but not yet
 // widened, so that a prefetched row costs as few registers as possible.
@@ -115,13 +97,6 @@ template <class C, bool SHIFTED> struct RowState {
     bool solid;
 };
 
-// Boundary data of open x boundaries, in the arithmetic precision.
-template <class C> struct OpenX {
-    bool on;
-    int nx;
-    C u_in, rho_in, rho_out, phi_wall;
-};
-
 template <class T, class C, bool SHIFTED>
 __device__ __forceinline__ void widen(RowState<C, SHIFTED> &r, const Raw<T> &raw, C gx, C gy,
                                       const OpenX<C> &ox, int xc) {
@@ -161,41 +136,6 @@ __device__ __forceinline__ C halo_phix(const Raw<T> &raw, C gx, const OpenX<C> &
 }
 
 static_assert(kStripWidth == 64, "one strip column per lane of a 64-wide wavefront");
-
-// DPP whole-wavefront shifts: lane i receives lane i-1 (shr) or lane i+1
-// (shl); the lane with no source keeps `old`.
-__device__ __forceinline__ float dpp_shr(float old, float src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
-                                                                  __builtin_bit_cast(int, src),
-                                                                  0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float dpp_shl(float old, float src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old),
-                                                                  __builtin_bit_cast(int, src),
-                                                                  0x130, 0xf, 0xf, false));
-}
-__device__ __forceinline__ uint32_t dpp_shr(uint32_t old, uint32_t src) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, 0x138, 0xf, 0xf, false);
-}
-__device__ __forceinline__ uint32_t dpp_shl(uint32_t old, uint32_t src) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, 0x130, 0xf, 0xf, false);
-}
-__device__ __forceinline__ double dpp_shr(double old, double src) {
-    const uint64_t o = __builtin_bit_cast(uint64_t, old), v = __builtin_bit_cast(uint64_t, src);
-    const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)v, 0x138, 0xf,
-                                                    0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(v >> 32),
-                                                    0x138, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double dpp_shl(double old, double src) {
-    const uint64_t o = __builtin_bit_cast(uint64_t, old), v = __builtin_bit_cast(uint64_t, src);
-    const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)v, 0x130, 0xf,
-                                                    0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(v >> 32),
-                                                    0x130, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
 
 // Store the FP16 population held in the low half of a register.
 template <class Acc>

@@ -28,6 +28,7 @@ import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SWEEP_SOURCES = ["paper_2312_10318_amd/csrc/sweep.hip", "paper_2312_10318_amd/csrc/lattice.hpp",
+                 "paper_2312_10318_amd/csrc/narrow.hip", "paper_2312_10318_amd/csrc/wave.hpp",
                  "paper_2312_10318_amd/csrc/kernels.hpp", "paper_2312_10318_amd/csrc/probe.hip"]
 COPY_BYTES = 1 << 30
 BYTES_PER_LU = {"f64": 144, "f32": 72, "f16": 36}
@@ -64,12 +65,16 @@ def _is_sweep(name):
             "sweep_tb2_kernel" in name or "sweep_tb2_batch_kernel" in name or
             "sweep_tb3_kernel" in name or "sweep_tb3_batch_kernel" in name or
             "sweep_batch_kernel" in name or
+            "narrow_kernel" in name or "narrow_batch_kernel" in name or
             "pattern_probe_kernel" in name)
 
 
 def updates_per_launch(kernel_name) -> int:
     """Time steps one launch of a sweep kernel advances the lattice by."""
     name = kernel_name or ""
+    narrow = re.search(r"narrow(?:_batch)?_kernel<\d, (\d)", name)
+    if narrow:
+        return int(narrow.group(1))
     return 3 if "sweep_tb3" in name else 2 if "sweep_tb2" in name else 1
 
 
