@@ -197,6 +197,13 @@ struct trt_sim {
     bool in_batch;
 };
 
+// How a batch member advances.
+enum MemberClass : char {
+    kOneStep = 0,   // one step per launch
+    kWide = 1,      // several per launch, 128-column windows
+    kNarrow = 2,    // several per launch, 64-column windows
+};
+
 struct trt_batch {
     std::vector<trt_sim *> sims;
     int storage;
@@ -224,18 +231,22 @@ struct trt_batch {
     // Outgrown tables and staging buffers, freed with the batch: freeing
     // them at once would wait for the launches queued on the stream.
     std::vector<void *> retired_dev, retired_host;
-    int nitems;  // one-step items: members of class 0, then of class 1
-    int parity;  // steps taken by the batch, mod 2 (with two-step launches:
-                 // the lattice parity of the class-0 members)
-    // Two time steps per launch for the members that allow it (class 1,
-    // two[k] = 1): their descriptors tiled for the two-step pass follow the
-    // n one-step ones, their two-step items follow the one-step items.
-    std::vector<char> two;
-    int nitems0;  // one-step items of class-0 members (a prefix of the list)
-    int nitems2;  // two-step items
-    int ndescs2;  // two-step descriptors (class-1 members)
-    bool deep2;   // two-step launches load two rows ahead
-    int k2;       // time steps per class-1 launch: 2, or 3 (FP32, steps_per_sweep 3)
+    int nitems;  // one-step items: members of class 0, then the others
+    int parity;  // steps taken by the batch, mod 2 (with launches of several
+                 // steps: the lattice parity of the class-0 members)
+    // How each member advances (MemberClass).  The descriptors of the members
+    // that take several steps per launch, tiled for their pass, follow the n
+    // one-step ones; their items follow the one-step items: those of the
+    // 128-column windows, then those of the 64-column windows without and with
+    // a link map.
+    std::vector<char> cls;
+    int nitems0;    // one-step items of class-0 members (a prefix of the list)
+    int nitems2;    // items of 128-column windows
+    int nnarrow[2]; // items of 64-column windows without, with a link map
+    int ndescs2;    // descriptors tiled for launches of several steps
+    bool deep2;     // two-step launches load two rows ahead
+    bool multi;     // some member takes several steps per launch
+    int k2;         // how many: 2 or 3
     int64_t steps;  // time steps since the tables were built
     int parity2;  // class-1 launches and one-step sweeps of class 1, mod 2
     hipStream_t cap_stream;
@@ -914,6 +925,81 @@ static hipError_t grow_pinned(E *&p, size_t &cap, size_t need, std::vector<void 
 }
 }  // extern "C++"
 
+extern "C++" {
+// The items of the members in 128-column windows (their descriptors come
+// first among those tiled for launches of several steps).
+template <class Order>
+static void batch_wide_items(trt_batch *b, const std::vector<size_t> &mem,
+                             std::vector<InstDesc> &descs, std::vector<int4> &items, Order order) {
+    const int valid2 = b->k2 == 3 ? trt::kTb3Valid : trt::kTb2Valid;
+    Launch l2 = b->launch;
+    if (l2.rows_per_wave <= 0) {
+        static const int kRows2[] = {32, 24, 16, 12, 8};
+        static const int kRows3[] = {32, 24, 20, 16, 12, 8};
+        const int *rows = b->k2 == 3 ? kRows3 : kRows2;
+        const int nrows = b->k2 == 3 ? 6 : 5;
+        const long long target = b->k2 == 3 ? 24576 : 32768;
+        l2.rows_per_wave = 8;
+        for (int i = 0; i < nrows; ++i) {
+            const int r = rows[i];
+            long long c = 0;
+            for (size_t k : mem)
+                c += (long long)((descs[k].nx + valid2 - 1) / valid2) *
+                     ((descs[k].ny + r - 1) / r);
+            if (c >= target) {
+                l2.rows_per_wave = r;
+                break;
+            }
+        }
+    }
+    const size_t from = items.size();
+    for (size_t j = 0; j < mem.size(); ++j) {
+        InstDesc d2 = b->k2 == 3 ? trt::tb3_desc(descs[mem[j]], l2)
+                                 : trt::tb2_desc(descs[mem[j]], l2);
+        descs.push_back(d2);
+        // the two-step kernel's descriptor table starts after the n
+        // one-step ones: its items name j (entry n + j of the whole table)
+        for (int r = 0; r < d2.rowblocks; ++r)
+            for (int c = 0; c < d2.strips; ++c)
+                items.push_back(make_int4((int)j, c, r, 2));
+    }
+    order(from);
+    b->nitems2 = (int)(items.size() - from);
+    b->deep2 = b->k2 == 2 &&
+               trt::tb2_batch_prefetch_rows(b->nitems2, b->storage, b->launch) == 2;
+}
+
+// The items of the members in 64-column windows: those without a link map,
+// then those with one.
+template <class Order>
+static void batch_narrow_items(trt_batch *b, const std::vector<size_t> &mem, int64_t nodes,
+                               size_t n, std::vector<InstDesc> &descs, std::vector<int4> &items,
+                               Order order) {
+    bool links = false;
+    for (size_t k : mem) links = links || descs[k].links != nullptr;
+    const int cap = trt::narrow_cap(b->storage, b->k2, links, nodes);
+    const int rows = trt::narrow_rows(b->storage, cap, [&](int r) {
+        int64_t w = 0;
+        for (size_t k : mem) w += trt::narrow_waves(descs[k], b->k2, r);
+        return w;
+    });
+    for (int l = 0; l < 2; ++l) {
+        const size_t from = items.size();
+        for (size_t k : mem) {
+            if ((descs[k].links != nullptr) != (l != 0)) continue;
+            const int j = (int)(descs.size() - n);
+            const InstDesc d = trt::narrow_desc(descs[k], b->k2, rows);
+            descs.push_back(d);
+            for (int r = 0; r < d.rowblocks; ++r)
+                for (int c = 0; c < d.strips; ++c) items.push_back(make_int4(j, c, r, 3));
+        }
+        order(from);
+        b->nnarrow[l] = (int)(items.size() - from);
+    }
+}
+
+}  // extern "C++"
+
 // (Re)build the work list and descriptor tables of the current members.  The
 // tables are copied from pinned staging buffers on the batch's stream, so no
 // device-wide wait is needed: launches already enqueued read the old tables
@@ -950,28 +1036,47 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
             d.rowblocks = (d.ny + d.rows - 1) / d.rows;
         }
     }
-    // class 1: members that take multi-step launches: three steps per launch
-    // in FP32 (unless two are asked for), two in FP16.  The 256-member
-    // benchmark batch (sides 64 to 1024), FP32: 155.4 GLUPS with three steps
-    // per launch against 118.0 with two -- its members are small, but
-    // together they far exceed the memory-side cache.
+    // How each member advances.  Class kWide: three steps per launch in FP32
+    // (unless two are asked for), two in FP16.  The 256-member benchmark batch
+    // (sides 64 to 1024), FP32: 155.4 GLUPS with three steps per launch against
+    // 118.0 with two -- its members are small, but together they far exceed
+    // the memory-side cache.  With rows and steps automatic: members that the
+    // 128-column passes do not take (FP64, link maps other than whole-row walls) are narrow, two steps
+    // per launch (FP32: as the wide members); and so are all members of a
+    // batch whose 128-column windows would not give two wavefronts per SIMD.
     const int sps = b->launch.steps_per_sweep;
+    const bool automatic = sps == 0 && b->launch.rows_per_wave == 0;
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
-    b->two.assign(n, 0);
-    if (b->launch.steps_per_sweep != 1)
-        for (size_t k = 0; k < n; ++k)
-            b->two[k] = (b->k2 == 3 ? trt::tb3_eligible(descs[k], b->sims[k]->prob.storage)
-                                    : trt::tb2_eligible(descs[k], b->sims[k]->prob.storage))
-                            ? 1
-                            : 0;
-    for (size_t k = 0; k < n; ++k) descs[k].cls = b->two[k];
+    int64_t wide_waves = 0, nodes = 0;
+    for (const InstDesc &d : descs) {
+        if (trt::tb2_eligible(d, b->storage))
+            wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
+        nodes += (int64_t)d.nx * d.ny;
+    }
+    const bool small = wide_waves < 2048;
+    b->cls.assign(n, kOneStep);
+    b->multi = false;
+    for (size_t k = 0; k < n; ++k) {
+        const InstDesc &d = descs[k];
+        const bool wide = sps != 1 && (b->k2 == 3 ? trt::tb3_eligible(d, b->storage)
+                                                  : trt::tb2_eligible(d, b->storage));
+        const bool narrow = automatic && trt::narrow_eligible(d, b->storage);
+        if (narrow && (!wide || small))
+            b->cls[k] = kNarrow;
+        else if (wide)
+            b->cls[k] = kWide;
+        b->multi = b->multi || b->cls[k] == kWide || b->cls[k] == kNarrow;
+        descs[k].cls = b->cls[k] != kOneStep ? 1 : 0;
+    }
     const int valid2 = b->k2 == 3 ? trt::kTb3Valid : trt::kTb2Valid;
     const auto cost = [&](const int4 &it) {
-        // two-step items (it.w == 2) index the two-step descriptors, which
-        // follow the n one-step ones
-        const InstDesc &d = descs[it.w == 2 ? n + (size_t)it.x : (size_t)it.x];
+        // items of several steps (it.w 2: 128-column windows, 3: 64) index the
+        // descriptors tiled for them, which follow the n one-step ones
+        const InstDesc &d = descs[it.w >= 2 ? n + (size_t)it.x : (size_t)it.x];
         const int rows = std::min(d.rows, d.ny - it.z * d.rows);
-        return (int64_t)rows * (it.w == 2 ? valid2 : trt::kStripWidth * d.cols);
+        return (int64_t)rows * (it.w == 2   ? valid2
+                                : it.w == 3 ? trt::narrow_valid(b->k2)
+                                            : trt::kStripWidth * d.cols);
     };
     const auto order = [&](size_t from) {
         // costliest first: rows in the block x columns per strip (stable, so
@@ -984,7 +1089,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     for (int cls = 0; cls < 2; ++cls) {
         const size_t from = items.size();
         for (size_t k = 0; k < n; ++k)
-            if (b->two[k] == cls)
+            if ((b->cls[k] != kOneStep) == (cls != 0))
                 for (int r = 0; r < descs[k].rowblocks; ++r)
                     for (int c = 0; c < descs[k].strips; ++c)
                         items.push_back(make_int4((int)k, c, r, cls));
@@ -1001,48 +1106,16 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // steps (ten rows of fill per block): the longest of 32, 24, 20, 16, 12,
     // 8 that gives 24576 items (FP32 152.7 / 154.5 / 155.4 / 153.8 / 147.2
     // GLUPS at 32 / 24 / 20 / 16 / 12 rows).  Else 8.), then their items
-    std::vector<size_t> mem;
-    for (size_t k = 0; k < n; ++k)
-        if (b->two[k]) mem.push_back(k);
-    b->nitems2 = 0;
-    b->ndescs2 = (int)mem.size();
+    std::vector<size_t> mem, narrow;
+    for (size_t k = 0; k < n; ++k) {
+        if (b->cls[k] == kWide) mem.push_back(k);
+        if (b->cls[k] == kNarrow) narrow.push_back(k);
+    }
+    b->nitems2 = b->nnarrow[0] = b->nnarrow[1] = 0;
     b->deep2 = false;
-    if (mem.empty()) return;
-    Launch l2 = b->launch;
-    if (l2.rows_per_wave <= 0) {
-        static const int kRows2[] = {32, 24, 16, 12, 8};
-        static const int kRows3[] = {32, 24, 20, 16, 12, 8};
-        const int *rows = b->k2 == 3 ? kRows3 : kRows2;
-        const int nrows = b->k2 == 3 ? 6 : 5;
-        const long long target = b->k2 == 3 ? 24576 : 32768;
-        l2.rows_per_wave = 8;
-        for (int i = 0; i < nrows; ++i) {
-            const int r = rows[i];
-            long long c = 0;
-            for (size_t k : mem)
-                c += (long long)((descs[k].nx + valid2 - 1) / valid2) *
-                     ((descs[k].ny + r - 1) / r);
-            if (c >= target) {
-                l2.rows_per_wave = r;
-                break;
-            }
-        }
-    }
-    const size_t from = items.size();
-    for (size_t j = 0; j < mem.size(); ++j) {
-        InstDesc d2 = b->k2 == 3 ? trt::tb3_desc(descs[mem[j]], l2)
-                                 : trt::tb2_desc(descs[mem[j]], l2);
-        descs.push_back(d2);
-        // the two-step kernel's descriptor table starts after the n
-        // one-step ones: its items name j (entry n + j of the whole table)
-        for (int r = 0; r < d2.rowblocks; ++r)
-            for (int c = 0; c < d2.strips; ++c)
-                items.push_back(make_int4((int)j, c, r, 2));
-    }
-    order(from);
-    b->nitems2 = (int)(items.size() - from);
-    b->deep2 = b->k2 == 2 &&
-               trt::tb2_batch_prefetch_rows(b->nitems2, b->storage, b->launch) == 2;
+    if (!mem.empty()) batch_wide_items(b, mem, descs, items, order);
+    if (!narrow.empty()) batch_narrow_items(b, narrow, nodes, n, descs, items, order);
+    b->ndescs2 = (int)(descs.size() - n);
 }
 
 static trt_status batch_build(trt_batch *b) {
@@ -1171,8 +1244,8 @@ trt_status trt_batch_get_tuning(const trt_batch *b, trt_tuning *t) {
     t->batch_items = b->launch.batch_items;
     t->batch_order = b->launch.batch_order;
     t->graph_steps = b->launch.graph_steps;
-    t->steps_per_sweep = b->nitems2 > 0 ? b->k2 : 1;
-    t->prefetch_rows = b->nitems2 > 0 ? (b->deep2 ? 2 : 1) : 0;
+    t->steps_per_sweep = b->multi ? b->k2 : 1;
+    t->prefetch_rows = b->multi ? (b->deep2 ? 2 : 1) : 0;
     return TRT_OK;
 }
 
@@ -1181,7 +1254,8 @@ static void batch_sync_members(trt_batch *b, int64_t steps, int64_t flips0, int6
     for (size_t k = 0; k < b->sims.size(); ++k) {
         trt_sim *s = b->sims[k];
         s->time += steps;
-        if (((b->two.empty() || !b->two[k]) ? flips0 : flips1) & 1) s->cur ^= 1;
+        const char c = b->cls.empty() ? (char)kOneStep : b->cls[k];
+        if ((c == kOneStep ? flips0 : flips1) & 1) s->cur ^= 1;
     }
 }
 
@@ -1196,13 +1270,20 @@ static hipError_t batch_single(const trt_batch *b, int f0, int f1, hipStream_t s
 // One unit of k2 steps: one k2-step launch of class 1 and k2 one-step
 // sweeps of class 0 (parities f0 and f1 at its start).
 static hipError_t batch_unit(const trt_batch *b, int f0, int f1, hipStream_t s) {
-    const size_t n = b->sims.size();
-    hipError_t e =
-        b->k2 == 3
-            ? trt::launch_sweep_tb3_batch(b->d_descs + n, b->ndescs2, b->d_items + b->nitems,
-                                          b->nitems2, b->storage, f1, b->launch, s)
-            : trt::launch_sweep_tb2_batch(b->d_descs + n, b->ndescs2, b->d_items + b->nitems,
-                                          b->nitems2, b->storage, f1, b->deep2, b->launch, s);
+    const InstDesc *descs = b->d_descs + b->sims.size();
+    const int4 *items = b->d_items + b->nitems;
+    hipError_t e = hipSuccess;
+    if (b->nitems2 > 0)
+        e = b->k2 == 3 ? trt::launch_sweep_tb3_batch(descs, b->ndescs2, items, b->nitems2,
+                                                     b->storage, f1, b->launch, s)
+                       : trt::launch_sweep_tb2_batch(descs, b->ndescs2, items, b->nitems2,
+                                                     b->storage, f1, b->deep2, b->launch, s);
+    items += b->nitems2;
+    for (int l = 0; l < 2 && e == hipSuccess; ++l) {
+        e = trt::launch_narrow_batch(descs, b->ndescs2, items, b->nnarrow[l], b->storage, b->k2,
+                                     l != 0, f1, b->launch, s);
+        items += b->nnarrow[l];
+    }
     for (int h = 0; h < b->k2 && e == hipSuccess && b->nitems0 > 0; ++h)
         e = trt::launch_sweep_batch(b->d_descs, b->d_items, b->nitems0, b->storage, b->mask,
                                     b->buf, f0 ^ (h & 1), f0 ^ (h & 1), b->launch, s);
@@ -1216,7 +1297,7 @@ static trt_status batch_capture(trt_batch *b, hipGraphExec_t &out, int64_t sweep
     release_graph(out);
     return capture(b->cap_stream, out, [&](hipStream_t cs) {
         for (int64_t k = 0; k < sweeps; ++k) {
-            hipError_t e = b->nitems2 > 0
+            hipError_t e = b->multi
                                ? batch_unit(b, (int)((k * b->k2) & 1), (int)(k & 1), cs)
                                : trt::launch_sweep_batch(b->d_descs, b->d_items, b->nitems,
                                                          b->storage, b->mask, b->buf, (int)(k & 1),
@@ -1287,7 +1368,7 @@ trt_status trt_batch_step(trt_batch *b, int64_t nsteps) {
     if (nsteps < 0) return fail(TRT_EINVAL, "nsteps must be >= 0");
     int64_t n = nsteps;
     if (n == 0) return TRT_OK;
-    if (b->nitems2 > 0) return batch_step_two(b, n);
+    if (b->multi) return batch_step_two(b, n);
     if (b->parity == 1) {
         TRT_HIP(trt::launch_sweep_batch(b->d_descs, b->d_items, b->nitems, b->storage, b->mask,
                                         b->buf, 1, 1, b->launch, b->stream));
@@ -1321,7 +1402,7 @@ trt_status trt_batch_diagnostics(trt_batch *b, double *out) {
     int64_t most = 0;
     for (const trt_sim *s : b->sims) most = std::max(most, (int64_t)s->desc.nx * s->desc.ny);
     TRT_HIP(trt::launch_diagnostics_batch(b->d_descs, (int)n, most, b->storage, b->parity,
-                                          b->nitems2 > 0 ? b->parity2 : b->parity, b->steps, out,
+                                          b->multi ? b->parity2 : b->parity, b->steps, out,
                                           b->stream));
     return TRT_OK;
 }

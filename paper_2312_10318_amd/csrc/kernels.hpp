@@ -179,6 +179,30 @@ struct NarrowPlan {
 NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l);
 // The instance tiled for the pass.
 InstDesc narrow_desc(const InstDesc &d, int k, int rows);
+// Wavefronts of a launch of k steps in blocks of r rows.
+inline int64_t narrow_waves(const InstDesc &d, int k, int r) {
+    return (int64_t)((d.nx + narrow_valid(k) - 1) / narrow_valid(k)) * ((d.ny + r - 1) / r);
+}
+// The most rows per block, and the rows from the wavefronts that r rows give
+// (see narrow_plan).
+inline int narrow_cap(int storage, int k, bool links, int64_t nodes) {
+    if (storage == ST_F64) return links ? 10 : 8;
+    if (storage == ST_F32) return k == 2 ? 8 : 16;
+    return nodes > 1024 * 1024 * 5 / 4 ? 24 : 6;
+}
+template <class W> int narrow_rows(int storage, int cap, W waves) {
+    const int64_t most = storage == ST_F64 ? 1024 : 2048;
+    // a single row per block only while that leaves one wavefront per SIMD
+    int r = waves(1) <= 1024 ? 1 : 2;
+    while (r < cap && waves(r) > most) ++r;
+    return r;
+}
+// k steps of the batch members named by items, as launch_sweep_tb2_batch
+// (descs tiled by narrow_desc; the members with a link map and those without
+// apart).
+hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
+                               int storage, int k, bool links, int flip, const Launch &l,
+                               hipStream_t stream);
 hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, int src,
                          hipStream_t stream);
 

@@ -94,8 +94,9 @@ struct InstDesc {
     // (u_in, 0) at density rho_in, pressure outlet at x = nx - 1 held at
     // rho_out; xbc = 0: periodic in x
     int32_t xbc;
-    // in a batch's table: the member's class (1: it takes launches of several
-    // steps) and its time when the table was built
+    // in a batch's table: how the member's lattices alternate (0: with the
+    // one-step launches, 1: with the launches of several steps) and its time
+    // when the table was built
     int32_t cls;
     int64_t time0;
     double u_in, rho_in, rho_out;

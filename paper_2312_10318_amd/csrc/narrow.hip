@@ -457,6 +457,29 @@ hipError_t launch_narrow_k(const InstDesc &t, int k, int src, int wpb, int remap
     return hipErrorInvalidValue;
 }
 
+template <int ST>
+hipError_t launch_narrow_batch_k(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
+                                 int k, bool links, int flip, const Launch &l, hipStream_t s) {
+    // one-wavefront workgroups while they spread over the CUs at once
+    const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
+    const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
+    const int r = l.xcd_remap;
+    if (k == 2 && links)
+        narrow_batch_kernel<ST, 2, true><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+    else if (k == 2)
+        narrow_batch_kernel<ST, 2, false><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+    else if constexpr (ST != ST_F64) {
+        if (k != 3) return hipErrorInvalidValue;
+        if (links)
+            narrow_batch_kernel<ST, 3, true><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+        else
+            narrow_batch_kernel<ST, 3, false><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool narrow_eligible(const InstDesc &d, int storage) {
@@ -481,6 +504,18 @@ hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, in
         case ST_F64: return launch_narrow_k<ST_F64>(t, p.k, src, p.waves_per_block, p.remap, stream);
         case ST_F32: return launch_narrow_k<ST_F32>(t, p.k, src, p.waves_per_block, p.remap, stream);
         case ST_F16: return launch_narrow_k<ST_F16>(t, p.k, src, p.waves_per_block, p.remap, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
+                               int storage, int k, bool links, int flip, const Launch &l,
+                               hipStream_t stream) {
+    if (nitems <= 0) return hipSuccess;
+    switch (storage) {
+        case ST_F64: return launch_narrow_batch_k<ST_F64>(descs, ndescs, items, nitems, k, links, flip, l, stream);
+        case ST_F32: return launch_narrow_batch_k<ST_F32>(descs, ndescs, items, nitems, k, links, flip, l, stream);
+        case ST_F16: return launch_narrow_batch_k<ST_F16>(descs, ndescs, items, nitems, k, links, flip, l, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -513,32 +548,24 @@ hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, in
 // rows 71.5, 16 and up over 73 us; 182 VGPRs with links keep two wavefronts
 // per SIMD, 1050^2: 8 rows 26.3, 10 rows 20.4).
 NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
-    NarrowPlan p = {0, 0, 0, 0};
+    const NarrowPlan p0 = {0, 0, 0, 0};
+    NarrowPlan p = p0;
     const bool automatic = l.rows_per_wave == 0 && l.waves_per_block == 0 && l.cols_per_lane == 0 &&
                            l.steps_per_sweep == 0 && l.prefetch_rows == 0;
     if (!automatic || !narrow_eligible(d, storage)) return p;
     const int64_t nodes = (int64_t)d.nx * d.ny;
     const bool wide = tb2_eligible(d, storage);  // the 128-column passes apply
     constexpr int64_t k1 = 1024;
-    int cap;
-    if (storage == ST_F64) {
-        p.k = 2;
-        cap = d.links ? 10 : 8;
-    } else if (storage == ST_F32) {
-        if (wide && nodes >= 2048 * 2048) return p;
-        p.k = nodes > (wide ? k1 * k1 : k1 * k1 / 2) ? 3 : 2;
-        cap = p.k == 2 ? 8 : 16;
-    } else {
-        if (wide && nodes > k1 * k1 * 5 / 4) return p;
-        p.k = 2;
-        cap = nodes > k1 * k1 * 5 / 4 ? 24 : 6;
+    p.k = 2;
+    if (storage == ST_F32) {
+        if (wide && nodes >= 2048 * 2048) return p0;
+        if (nodes > (wide ? k1 * k1 : k1 * k1 / 2)) p.k = 3;
+    } else if (storage == ST_F16 && wide && nodes > k1 * k1 * 5 / 4) {
+        return p0;
     }
-    const int64_t strips = (d.nx + narrow_valid(p.k) - 1) / narrow_valid(p.k);
-    const auto waves = [&](int r) { return strips * ((d.ny + r - 1) / r); };
-    const int64_t most = storage == ST_F64 ? 1024 : 2048;
-    // a single row per block only while that leaves one wavefront per SIMD
-    p.rows = waves(1) <= 1024 ? 1 : 2;
-    while (p.rows < cap && waves(p.rows) > most) ++p.rows;
+    const int cap = narrow_cap(storage, p.k, d.links != nullptr, nodes);
+    const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };
+    p.rows = narrow_rows(storage, cap, waves);
     p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
     p.remap = l.remap_asked ? l.xcd_remap : 1;
     return p;

@@ -123,3 +123,42 @@ def test_a_set_shape_keeps_the_passes_it_describes(L):
     lat = L.Lattice(256, 15, 0.7, 1.0, storage="f64")
     assert lat.tuning()[5] == 1
     lat.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("large", [False, True])
+def test_batches_equal_one_step_batches(L, storage, large):
+    """Members of every kind in one batch (with `large`, one big enough that
+    the open FP32 and FP16 members keep the 128-column windows), over splits
+    that leave single steps and pairs, with diagnostics in between and a
+    membership change."""
+    specs = [("open", 130, 64), ("cylinder", 117, 60), ("walls", 65, 33), ("obstacle", 140, 41),
+             ("open", 257, 51), ("random", 61, 17), ("open", 200, 9)]
+    if large:
+        specs.append(("open", 1400, 1500))
+    runs = []
+    for sps in (1, 0):
+        lats = []
+        for kind, nx, ny in specs:
+            mask, g, inflow = _problem(kind, nx, ny)
+            lat = L.Lattice(nx, ny, 0.8, 1.2, g=g, mask=mask, storage=storage, inflow=inflow)
+            lat.set_populations(inputs.random_populations(np.random.default_rng(nx), (ny, nx)))
+            lats.append(lat)
+        b = L.Batch(lats)
+        b.set_tuning(steps_per_sweep=sps, graph_steps=4)
+        assert b.tuning()[7] == (1 if sps else 3 if storage == "f32" else 2)
+        diags = []
+        for n in (1, 2, 5, 6, 13):
+            b.step(n)
+            diags.append(b.diagnostics())
+        b.update(lats[1:])
+        b.step(4)
+        diags.append(b.diagnostics())
+        b.close()
+        runs.append(([(m.get_populations().cpu().numpy(), m.state()[1]) for m in lats], diags))
+        for m in lats:
+            m.close()
+    for k, ((a, ta), (c, tc)) in enumerate(zip(*(r[0] for r in runs))):
+        say("case: member %d %s: time %d/%d, differs at %d" % (k, storage, ta, tc, int((a != c).sum())))
+        assert ta == tc == (31 if k else 27) and np.array_equal(a, c)
+    assert all(np.array_equal(a, c) for a, c in zip(*(r[1] for r in runs)))
