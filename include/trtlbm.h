@@ -125,8 +125,10 @@ typedef struct {
  * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1100^2 nodes.
  * trt_get_tuning then reports that pass's rows, wavefronts, steps and
  * prefetch (cols_per_lane stays the one-step sweeps').  Setting any of these
- * fields asks for the passes they describe.  Every choice gives the same
- * bits. */
+ * fields asks for the passes they describe.  Of those lattices, the ones of at
+ * most 1024 nodes advance all the steps of a call in one launch, in one
+ * workgroup and in place (the reported shape is then unused).  Every choice
+ * gives the same bits. */
 typedef struct {
     int32_t rows_per_wave;   /* rows one wavefront marches through, 1..4096 (0: automatic) */
     int32_t waves_per_block; /* wavefronts per workgroup: 1, 2, 4, 8 or 16 (0: automatic); the
@@ -247,7 +249,8 @@ trt_status trt_get_populations(trt_sim *s, double *f);
 /* Advance nsteps >= 0 time steps (Eq. 2 followed by streaming), enqueued on
  * the stream as replays of captured HIP graphs (see trt_tuning.graph_steps)
  * plus at most three plain launches; two or three time steps per launch
- * where trt_tuning.steps_per_sweep allows it.  Any split of the steps, and
+ * where trt_tuning.steps_per_sweep allows it, and as one plain launch per
+ * 8192 steps for lattices of at most 1024 nodes (see trt_tuning).  Any split of the steps, and
  * any number of steps per launch, gives the same bits. */
 trt_status trt_step(trt_sim *s, int64_t nsteps);
 

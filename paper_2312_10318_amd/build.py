@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtrtlbm.so")
-SOURCES = ["api.hip", "sweep.hip", "narrow.hip", "fields.hip", "probe.hip"]
+SOURCES = ["api.hip", "sweep.hip", "narrow.hip", "resident.hip", "fields.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [

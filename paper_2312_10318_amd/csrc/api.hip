@@ -185,6 +185,7 @@ struct trt_sim {
     hipStream_t stream;
     InstDesc desc;  // desc.cur stays 0: the lattice read is passed per launch
     Launch launch;
+    bool resident;           // every step of a call in one launch (resident.hip)
     trt::NarrowPlan narrow;  // one column per lane, several steps per launch (k = 0: not taken)
     int cur;        // lattice holding the current state
     int64_t time;
@@ -202,6 +203,7 @@ enum MemberClass : char {
     kOneStep = 0,   // one step per launch
     kWide = 1,      // several per launch, 128-column windows
     kNarrow = 2,    // several per launch, 64-column windows
+    kResident = 3,  // every step of a call in one launch
 };
 
 struct trt_batch {
@@ -238,11 +240,12 @@ struct trt_batch {
     // that take several steps per launch, tiled for their pass, follow the n
     // one-step ones; their items follow the one-step items: those of the
     // 128-column windows, then those of the 64-column windows without and with
-    // a link map.
+    // a link map; then one entry per resident member.
     std::vector<char> cls;
     int nitems0;    // one-step items of class-0 members (a prefix of the list)
     int nitems2;    // items of 128-column windows
     int nnarrow[2]; // items of 64-column windows without, with a link map
+    int nresident, resident_nodes;  // resident members, the largest one's nodes
     int ndescs2;    // descriptors tiled for launches of several steps
     bool deep2;     // two-step launches load two rows ahead
     bool multi;     // some member takes several steps per launch
@@ -378,6 +381,16 @@ trt_status sim_capture(trt_sim *s, hipGraphExec_t &out, int64_t sweeps) {
         }
         return hipSuccess;
     });
+}
+
+// Whether a lattice is small enough to stay in one workgroup's LDS for a
+// whole call (where its launch shape is automatic: narrow_plan's k > 0): one
+// thread per node is what a workgroup holds, and at the largest, 32 x 32, a
+// step takes 1.33 / 0.79 / 0.88 us (FP64 / FP32 / FP16) against the 2.4 - 3.3
+// us of passes with a launch per one to three steps (41 x 25, one node more:
+// 2.83 / 2.44 / 3.21).
+bool resident_size(const InstDesc &d) {
+    return (int64_t)d.nx * d.ny <= trt::kResidentNodes;
 }
 
 trt_status check_sim(const trt_sim *s) {
@@ -564,6 +577,7 @@ trt_status trt_create(const trt_problem *p, void *f_a, void *f_b, void *hip_stre
     }
     trt::tile(d, s->launch, p->storage);
     s->narrow = trt::narrow_plan(d, p->storage, s->launch);
+    s->resident = s->narrow.k && resident_size(d);
     // the capture stream is created at the first capture (batch members never
     // capture their own step)
     *out = s;
@@ -579,6 +593,7 @@ trt_status trt_set_tuning(trt_sim *s, const trt_tuning *t) {
     s->launch = l;
     trt::tile(s->desc, l, s->prob.storage);
     s->narrow = trt::narrow_plan(s->desc, s->prob.storage, l);
+    s->resident = s->narrow.k && resident_size(s->desc);
     release_graphs(s->graphs);
     return TRT_OK;
 }
@@ -646,6 +661,11 @@ trt_status trt_step(trt_sim *s, int64_t nsteps) {
     if (nsteps == 0) return TRT_OK;
     const int st = s->prob.storage;
     const bool m = s->prob.mask != nullptr;
+    if (s->resident) {
+        TRT_HIP(trt::launch_resident(s->desc, st, s->cur, nsteps, s->stream));
+        s->time += nsteps;
+        return TRT_OK;
+    }
     if (s->cur == 1) {
         TRT_HIP(trt::launch_sweep(s->desc, st, m, 1, s->launch, s->stream));
         s->cur = 0;
@@ -703,6 +723,7 @@ trt_status trt_prepare_steps(trt_sim *s, int64_t nsteps) {
     if (check_sim(s) != TRT_OK) return TRT_EINVAL;
     if (nsteps < 0) return fail(TRT_EINVAL, "nsteps must be >= 0");
     if (s->in_batch) return fail(TRT_ESTATE, "simulation is a batch member");
+    if (s->resident) return TRT_OK;  // no graphs
     // the launches trt_step would replay as graphs (see there)
     int64_t n = nsteps;
     if (s->cur == 1 && n > 0) --n;
@@ -1040,8 +1061,9 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // (unless two are asked for), two in FP16.  The 256-member benchmark batch
     // (sides 64 to 1024), FP32: 155.4 GLUPS with three steps per launch against
     // 118.0 with two -- its members are small, but together they far exceed
-    // the memory-side cache.  With rows and steps automatic: members that the
-    // 128-column passes do not take (FP64, link maps other than whole-row walls) are narrow, two steps
+    // the memory-side cache.  With rows and steps automatic: members of at most
+    // kResidentNodes nodes are resident; those the 128-column passes do not
+    // take (FP64, link maps other than whole-row walls) are narrow, two steps
     // per launch (FP32: as the wide members); and so are all members of a
     // batch whose 128-column windows would not give two wavefronts per SIMD.
     const int sps = b->launch.steps_per_sweep;
@@ -1049,7 +1071,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
     int64_t wide_waves = 0, nodes = 0;
     for (const InstDesc &d : descs) {
-        if (trt::tb2_eligible(d, b->storage))
+        if (trt::tb2_eligible(d, b->storage) && !resident_size(d))
             wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
         nodes += (int64_t)d.nx * d.ny;
     }
@@ -1061,12 +1083,14 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
         const bool wide = sps != 1 && (b->k2 == 3 ? trt::tb3_eligible(d, b->storage)
                                                   : trt::tb2_eligible(d, b->storage));
         const bool narrow = automatic && trt::narrow_eligible(d, b->storage);
-        if (narrow && (!wide || small))
+        if (narrow && resident_size(d))
+            b->cls[k] = kResident;
+        else if (narrow && (!wide || small))
             b->cls[k] = kNarrow;
         else if (wide)
             b->cls[k] = kWide;
         b->multi = b->multi || b->cls[k] == kWide || b->cls[k] == kNarrow;
-        descs[k].cls = b->cls[k] != kOneStep ? 1 : 0;
+        descs[k].cls = b->cls[k] == kResident ? 2 : (b->cls[k] != kOneStep ? 1 : 0);
     }
     const int valid2 = b->k2 == 3 ? trt::kTb3Valid : trt::kTb2Valid;
     const auto cost = [&](const int4 &it) {
@@ -1089,7 +1113,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     for (int cls = 0; cls < 2; ++cls) {
         const size_t from = items.size();
         for (size_t k = 0; k < n; ++k)
-            if ((b->cls[k] != kOneStep) == (cls != 0))
+            if (b->cls[k] != kResident && (b->cls[k] != kOneStep) == (cls != 0))
                 for (int r = 0; r < descs[k].rowblocks; ++r)
                     for (int c = 0; c < descs[k].strips; ++c)
                         items.push_back(make_int4((int)k, c, r, cls));
@@ -1116,6 +1140,13 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     if (!mem.empty()) batch_wide_items(b, mem, descs, items, order);
     if (!narrow.empty()) batch_narrow_items(b, narrow, nodes, n, descs, items, order);
     b->ndescs2 = (int)(descs.size() - n);
+    b->nresident = b->resident_nodes = 0;
+    for (size_t k = 0; k < n; ++k)
+        if (b->cls[k] == kResident) {
+            items.push_back(make_int4((int)k, 0, 0, 0));
+            ++b->nresident;
+            b->resident_nodes = std::max(b->resident_nodes, descs[k].nx * descs[k].ny);
+        }
 }
 
 static trt_status batch_build(trt_batch *b) {
@@ -1255,7 +1286,7 @@ static void batch_sync_members(trt_batch *b, int64_t steps, int64_t flips0, int6
         trt_sim *s = b->sims[k];
         s->time += steps;
         const char c = b->cls.empty() ? (char)kOneStep : b->cls[k];
-        if ((c == kOneStep ? flips0 : flips1) & 1) s->cur ^= 1;
+        if (c != kResident && ((c == kOneStep ? flips0 : flips1) & 1)) s->cur ^= 1;
     }
 }
 
@@ -1368,6 +1399,16 @@ trt_status trt_batch_step(trt_batch *b, int64_t nsteps) {
     if (nsteps < 0) return fail(TRT_EINVAL, "nsteps must be >= 0");
     int64_t n = nsteps;
     if (n == 0) return TRT_OK;
+    if (b->nresident > 0) {
+        // independent of the other members: all the call's steps at once
+        const int4 *members = b->d_items + b->nitems + b->nitems2 + b->nnarrow[0] + b->nnarrow[1];
+        TRT_HIP(trt::launch_resident_batch(b->d_descs, members, b->nresident, b->resident_nodes,
+                                           b->storage, n, b->stream));
+        if (b->nitems == 0) {
+            batch_sync_members(b, n, 0, 0);
+            return TRT_OK;
+        }
+    }
     if (b->multi) return batch_step_two(b, n);
     if (b->parity == 1) {
         TRT_HIP(trt::launch_sweep_batch(b->d_descs, b->d_items, b->nitems, b->storage, b->mask,

@@ -281,7 +281,8 @@ __global__ __launch_bounds__(kDiagThreads) void diag_batch_kernel(
     const InstDesc d = descs[first + blockIdx.y];
     const int blocks = diag_blocks((int64_t)d.nx * d.ny);
     if ((int)blockIdx.x >= blocks) return;
-    diag_block<ST>(d, d.cur ^ (d.cls ? flip1 : flip0), blockIdx.x, blocks, d.partials);
+    const int flip = d.cls == 0 ? flip0 : (d.cls == 1 ? flip1 : 0);
+    diag_block<ST>(d, d.cur ^ flip, blockIdx.x, blocks, d.partials);
 }
 
 __global__ __launch_bounds__(kDiagThreads) void diag_batch_final_kernel(

@@ -206,6 +206,15 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, int src,
                          hipStream_t stream);
 
+// Any number of steps of one lattice of at most kResidentNodes nodes in one
+// launch (resident.hip), in place: lattice src is read and written.
+constexpr int kResidentNodes = 1024;
+hipError_t launch_resident(const InstDesc &d, int storage, int src, int64_t steps,
+                           hipStream_t stream);
+// The same for the n batch members members[0 .. n).x of the table descs, of
+// at most most_nodes nodes each, on the lattices descs[].cur.
+hipError_t launch_resident_batch(const InstDesc *descs, const int4 *members, int n, int most_nodes,
+                                 int storage, int64_t steps, hipStream_t stream);
 // The access-pattern probe (a measurement aid): one launch moves the lattice
 // `src` to the other one with the two-column sweep's loads, stores, launch
 // shape and barriers and none of its arithmetic.  Only for two-column
@@ -239,7 +248,7 @@ int diag_partial_count();
 hipError_t launch_diagnostics(const InstDesc &d, int storage, int src, double *partials,
                               double *out, double time, hipStream_t stream);
 // Diagnostics of the n members of a batch (descs: its device table): member
-// k, which reads buf[cur ^ (cls ? flip1 : flip0)] and is `steps` steps past
+// k, which reads buf[cur ^ flip0] (cls 0), buf[cur ^ flip1] (1) or buf[cur] and is `steps` steps past
 // its time0, writes out[k][TRT_NDIAG].  most_nodes: the largest member's.
 hipError_t launch_diagnostics_batch(const InstDesc *descs, int n, int64_t most_nodes, int storage,
                                     int flip0, int flip1, int64_t steps, double *out,

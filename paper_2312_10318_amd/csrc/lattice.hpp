@@ -95,8 +95,8 @@ struct InstDesc {
     // rho_out; xbc = 0: periodic in x
     int32_t xbc;
     // in a batch's table: how the member's lattices alternate (0: with the
-    // one-step launches, 1: with the launches of several steps) and its time
-    // when the table was built
+    // one-step launches, 1: with the launches of several steps, 2: not at
+    // all) and its time when the table was built
     int32_t cls;
     int64_t time0;
     double u_in, rho_in, rho_out;

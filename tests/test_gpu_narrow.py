@@ -41,7 +41,7 @@ def _problem(kind, nx, ny):
 # widths: narrower than a window, one and two windows of 58 or 54 columns
 # and one column either side, the link summary's 64-column edges, odd ones;
 # heights: the fewest rows, blocks with a remainder
-SIZES = [(3, 16), (54, 19), (58, 17), (64, 40), (65, 33), (116, 70), (117, 16), (130, 64),
+SIZES = [(3, 350), (54, 19), (58, 18), (64, 40), (65, 33), (116, 70), (117, 16), (130, 64),
          (257, 51), (301, 90)]
 
 
