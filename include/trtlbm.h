@@ -122,7 +122,7 @@ typedef struct {
  * pass of two or three time steps per launch with one column per lane, which
  * applies to every storage, mask and boundary within 4 GiB: FP64 lattices,
  * lattices with a mask that does not fill whole rows or with open x
- * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1100^2 nodes.
+ * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1600^2 nodes.
  * trt_get_tuning then reports that pass's rows, wavefronts, steps and
  * prefetch (cols_per_lane stays the one-step sweeps').  Setting any of these
  * fields asks for the passes they describe.  Of those lattices, the ones of at
@@ -171,7 +171,8 @@ typedef struct {
     int32_t prefetch_rows;   /* two-step pass: how many rows ahead of their use its loads
                                 are issued, 1 or 2 (0: automatic -- 2 for FP32 launches of
                                 at least 4096 wavefronts, else 1; the three-step pass always
-                                loads one row ahead).  Two rows ahead keeps
+                                loads one row ahead; the one-column pass, see above, two
+                                for FP16 and for launches of at most 2048 wavefronts).  Two rows ahead keeps
                                 more loads in flight per wavefront but needs more
                                 registers, so fewer wavefronts fit on a SIMD.  No effect on
                                 results. */

@@ -611,7 +611,7 @@ trt_status trt_get_tuning(const trt_sim *s, trt_tuning *t) {
         t->rows_per_wave = s->narrow.rows;
         t->waves_per_block = s->narrow.waves_per_block;
         t->xcd_remap = s->narrow.remap;
-        t->prefetch_rows = 1;
+        t->prefetch_rows = s->narrow.depth;
         return TRT_OK;
     }
     t->rows_per_wave = ks == 3   ? trt::tb3_desc(s->desc, s->launch).rows
@@ -1065,7 +1065,11 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // kResidentNodes nodes are resident; those the 128-column passes do not
     // take (FP64, link maps other than whole-row walls) are narrow, two steps
     // per launch (FP32: as the wide members); and so are all members of a
-    // batch whose 128-column windows would not give two wavefronts per SIMD.
+    // batch too small for 128-column windows, by their number in blocks of 8
+    // rows (us per step, wide / narrow: FP32 93 windows 9.5 / 3.9, 1163 15.6 /
+    // 10.2, 3373 28.9 / 25.6, 4826 37.1 / 34.2, the 48-member sweep of 12 M nodes
+    // 104.4 / 107.6; FP16 93 9.9 / 4.3, 1163 15.2 / 11.8, 3373 26.5 / 23.2, 4826
+    // 31.3 / 31.9).
     const int sps = b->launch.steps_per_sweep;
     const bool automatic = sps == 0 && b->launch.rows_per_wave == 0;
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
@@ -1075,7 +1079,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
             wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
         nodes += (int64_t)d.nx * d.ny;
     }
-    const bool small = wide_waves < 2048;
+    const bool small = wide_waves < (b->storage == trt::ST_F32 ? 8192 : 4096);
     b->cls.assign(n, kOneStep);
     b->multi = false;
     for (size_t k = 0; k < n; ++k) {

@@ -174,7 +174,7 @@ constexpr int kNarrowMinRows = 16;
 bool narrow_eligible(const InstDesc &d, int storage);
 // The launch shape under which a lattice takes the pass; k = 0: it does not.
 struct NarrowPlan {
-    int k, rows, waves_per_block, remap;
+    int k, rows, waves_per_block, remap, depth;
 };
 NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l);
 // The instance tiled for the pass.
@@ -188,7 +188,13 @@ inline int64_t narrow_waves(const InstDesc &d, int k, int r) {
 inline int narrow_cap(int storage, int k, bool links, int64_t nodes) {
     if (storage == ST_F64) return links ? 10 : 8;
     if (storage == ST_F32) return k == 2 ? 8 : 16;
-    return nodes > 1024 * 1024 * 5 / 4 ? 24 : 6;
+    return nodes > 1024 * 1024 * 5 / 4 ? 12 : 5;
+}
+// Rows ahead of their use that a launch of `waves` wavefronts loads: two where
+// a wavefront is alone on its SIMD or nearly so, and FP16 always (see
+// narrow_plan).
+inline int narrow_depth(int storage, int64_t waves) {
+    return storage == ST_F16 || waves <= 2048 ? 2 : 1;
 }
 template <class W> int narrow_rows(int storage, int cap, W waves) {
     const int64_t most = storage == ST_F64 ? 1024 : 2048;

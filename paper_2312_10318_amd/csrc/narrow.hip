@@ -83,6 +83,13 @@ template <class C> struct Consts {
           gx(uniform((C)d.gx)), gy(uniform((C)d.gy)) {}
 };
 
+// A row's link summary entries, as loaded (or-ed where they are used, so that
+// the scalar loads' wait falls there).
+struct RowFlags {
+    uint32_t a, b, c;
+    __device__ __forceinline__ uint32_t any() const { return a | b | c; }
+};
+
 // What a wavefront needs of its lattice.
 template <int ST, bool LINK> struct NarrowCtx {
     using T = typename Store<ST>::T;
@@ -99,15 +106,56 @@ template <int ST, bool LINK> struct NarrowCtx {
     bool store;
     OpenX<C> ox;
 
-    __device__ __forceinline__ uint32_t summary(int y) const {
-        if constexpr (!LINK) return 0u;
+    // row y's summary entries
+    __device__ __forceinline__ RowFlags summary(int y) const {
+        if constexpr (!LINK) return RowFlags{0u, 0u, 0u};
         const int64_t r = (int64_t)y * nsum;
-        return sum[r + s0] | sum[r + s1] | sum[r + s2];
+        return RowFlags{sum[r + s0], sum[r + s1], sum[r + s2]};
     }
     // the codes of row y's nodes (0 where the row has no links)
     __device__ __forceinline__ uint32_t codes(int y, uint32_t flagged) const {
         if constexpr (!LINK) return 0u;
         return flagged ? la.ld1((uint32_t)((int64_t)y * lpitch), (uint32_t)col.xc) : 0u;
+    }
+};
+
+// The link data of the rows a pipeline is about to load, in their order: the
+// codes of the next DEPTH rows (issued DEPTH rows before the loads whose
+// addresses they pick, ahead of populations that are waited for first) and the
+// summary of the row after those, so neither is waited for where it is issued.
+template <int ST, bool LINK, int DEPTH> struct LinkQueue {
+    uint32_t code[DEPTH], flagged[DEPTH];
+    RowFlags ahead;
+    int row;  // the row `ahead` describes
+
+    // from the first row to load
+    __device__ __forceinline__ void start(const NarrowCtx<ST, LINK> &c, int y) {
+        if constexpr (LINK) {
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                flagged[i] = c.summary(y).any();
+                code[i] = c.codes(y, flagged[i]);
+                y = y + 1 == c.ny ? 0 : y + 1;
+            }
+            row = y;
+            ahead = c.summary(row);
+        }
+    }
+    // the link data of the next row to load, into r
+    __device__ __forceinline__ void take(NarrowRow<ST, LINK> &r, const NarrowCtx<ST, LINK> &c) {
+        if constexpr (LINK) {
+            r.code = code[0];
+            r.flagged = flagged[0];
+#pragma unroll
+            for (int i = 0; i + 1 < DEPTH; ++i) {
+                code[i] = code[i + 1];
+                flagged[i] = flagged[i + 1];
+            }
+            flagged[DEPTH - 1] = ahead.any();
+            code[DEPTH - 1] = c.codes(row, flagged[DEPTH - 1]);
+            row = row + 1 == c.ny ? 0 : row + 1;
+            ahead = c.summary(row);
+        }
     }
 };
 
@@ -295,12 +343,12 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
 // One pipeline row y: the first step's coefficients of gathered row
 // y + 2 K - 1, whose registers then take the loads of row yload (when
 // `load`), and the later parts (narrow_step).
-template <int ST, int K, bool LINK, bool FILL>
+template <int ST, int K, bool LINK, bool FILL, int DEPTH>
 __device__ __forceinline__ void narrow_row(NarrowState<ST, K, LINK> &s, NarrowRow<ST, LINK> &row,
+                                           LinkQueue<ST, LINK, DEPTH> &q,
                                            const NarrowCtx<ST, LINK> &c,
                                            const Consts<typename Store<ST>::C> &rt, int y,
-                                           bool load, int yload, uint32_t &next_flag,
-                                           uint32_t &next_code, int stage) {
+                                           bool load, int yload, int stage) {
     using C = typename Store<ST>::C;
     Coeffs<C> k;
     uint32_t code = 0u;
@@ -315,23 +363,15 @@ __device__ __forceinline__ void narrow_row(NarrowState<ST, K, LINK> &s, NarrowRo
         s.code[0] = (s.code[0] << 16) | code;
     }
     if (load) {
-        if constexpr (LINK) {
-            // the codes of the row after this one go out ahead of this row's
-            // populations, which are waited for first
-            row.code = next_code;
-            row.flagged = next_flag;
-            const int y1 = (yload + 1 == c.ny) ? 0 : yload + 1;
-            next_flag = c.summary(y1);
-            next_code = c.codes(y1, next_flag);
-        }
+        q.take(row, c);
         narrow_load<ST, LINK>(row, c, yload);
     }
     const C py = narrow_coeffs<ST, LINK>(k, f, code, c, rt);
     narrow_step<0, ST, K, LINK, FILL>(s, k, py, c, rt, y, stage);
 }
 
-// One window through one row block.
-template <int ST, int K, bool LINK>
+// One window through one row block, the loads DEPTH rows ahead of their use.
+template <int ST, int K, bool LINK, int DEPTH>
 __device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int rb, int srcsel) {
     using T = typename Store<ST>::T;
     using C = typename Store<ST>::C;
@@ -387,30 +427,51 @@ __device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int r
     const auto wrap_row = [&](int v) { v %= ny; return v < 0 ? v + ny : v; };
 
     NarrowState<ST, K, LINK> s{};
-    NarrowRow<ST, LINK> row;
-    // the first gathered row, y0 - edge, and the codes of the row after it
-    const int first = wrap_row(y0 - edge), second = wrap_row(y0 - edge + 1);
-    row.flagged = c.summary(first);
-    row.code = c.codes(first, row.flagged);
-    uint32_t next_flag = c.summary(second), next_code = c.codes(second, next_flag);
-    narrow_load<ST, LINK>(row, c, first);
-    int y = y0 - 2 * edge;
-    int yl = second;  // the row to load next, y + 2 K wrapped
-    for (int i = 0; i < 2 * edge; ++i, ++y) {
-        narrow_row<ST, K, LINK, true>(s, row, c, rt, y, y + 2 * K <= y1 + edge - 1, yl, next_flag,
-                                      next_code, i >> 1);
-        yl = yl + 1 == ny ? 0 : yl + 1;
+    NarrowRow<ST, LINK> row[DEPTH];
+    LinkQueue<ST, LINK, DEPTH> q;
+    int yl = wrap_row(y0 - edge);  // the row to load next
+    const auto next = [&]() { yl = yl + 1 == ny ? 0 : yl + 1; };
+    q.start(c, yl);
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+        q.take(row[i], c);
+        narrow_load<ST, LINK>(row[i], c, yl);
+        next();
     }
-    for (; y < y1; ++y) {
-        narrow_row<ST, K, LINK, false>(s, row, c, rt, y, y + 2 * K <= y1 + edge - 1, yl,
-                                       next_flag, next_code, 2 * K);
-        yl = yl + 1 == ny ? 0 : yl + 1;
+    // pipeline row y gathers row y + edge and loads row y + edge + DEPTH while
+    // the block needs it (rows up to y1 + edge - 1); buffers are named
+    // statically (a run-time index would move them to scratch memory)
+    const auto ld = [&](int y) { return y + DEPTH <= y1 - 1; };
+    int y = y0 - 2 * edge;
+    if constexpr (DEPTH == 1) {
+        for (int i = 0; i < 2 * edge; ++i, ++y) {
+            narrow_row<ST, K, LINK, true, DEPTH>(s, row[0], q, c, rt, y, ld(y), yl, i >> 1);
+            next();
+        }
+        for (; y < y1; ++y) {
+            narrow_row<ST, K, LINK, false, DEPTH>(s, row[0], q, c, rt, y, ld(y), yl, 2 * K);
+            next();
+        }
+    } else {
+        for (int i = 0; i < 2 * edge; i += 2, y += 2) {
+            narrow_row<ST, K, LINK, true, DEPTH>(s, row[0], q, c, rt, y, ld(y), yl, i >> 1);
+            next();
+            narrow_row<ST, K, LINK, true, DEPTH>(s, row[1], q, c, rt, y + 1, ld(y + 1), yl, i >> 1);
+            next();
+        }
+        for (; y + 1 < y1; y += 2) {
+            narrow_row<ST, K, LINK, false, DEPTH>(s, row[0], q, c, rt, y, ld(y), yl, 2 * K);
+            next();
+            narrow_row<ST, K, LINK, false, DEPTH>(s, row[1], q, c, rt, y + 1, ld(y + 1), yl, 2 * K);
+            next();
+        }
+        if (y < y1) narrow_row<ST, K, LINK, false, DEPTH>(s, row[0], q, c, rt, y, ld(y), yl, 2 * K);
     }
 }
 
 constexpr int kNarrowMaxWaves = 4;
 
-template <int ST, int K, bool LINK>
+template <int ST, int K, bool LINK, int DEPTH>
 __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(InstDesc d, int srcsel,
                                                                      int remap) {
     int b = blockIdx.x;
@@ -419,11 +480,11 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(InstDesc d
     const int wave = b * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave >= d.strips * d.rowblocks) return;
     const int rb = wave / d.strips;
-    narrow_strip<ST, K, LINK>(d, wave - rb * d.strips, rb, srcsel);
+    narrow_strip<ST, K, LINK, DEPTH>(d, wave - rb * d.strips, rb, srcsel);
 }
 
 // Batched: wavefront w takes item w = (member, window, row block, -).
-template <int ST, int K, bool LINK>
+template <int ST, int K, bool LINK, int DEPTH>
 __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_batch_kernel(
     const InstDesc *__restrict__ descs, int ndescs, const int4 *__restrict__ items, int nitems,
     int flip, int remap) {
@@ -435,25 +496,29 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_batch_kernel(
     const int4 it = items[wave];
     if ((unsigned)it.x >= (unsigned)ndescs) return;
     const InstDesc d = descs[it.x];
-    narrow_strip<ST, K, LINK>(d, it.y, it.z, d.cur ^ flip);
+    narrow_strip<ST, K, LINK, DEPTH>(d, it.y, it.z, d.cur ^ flip);
 }
 
 template <int ST, int K>
-hipError_t launch_narrow_t(const InstDesc &t, int src, int wpb, int remap, hipStream_t s) {
+hipError_t launch_narrow_t(const InstDesc &t, int src, int wpb, int remap, int depth, hipStream_t s) {
     const int waves = t.strips * t.rowblocks;
     const int blocks = (waves + wpb - 1) / wpb;
-    if (t.links)
-        narrow_kernel<ST, K, true><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+    if (depth == 2 && t.links)
+        narrow_kernel<ST, K, true, 2><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+    else if (depth == 2)
+        narrow_kernel<ST, K, false, 2><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+    else if (t.links)
+        narrow_kernel<ST, K, true, 1><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
     else
-        narrow_kernel<ST, K, false><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+        narrow_kernel<ST, K, false, 1><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
     return hipGetLastError();
 }
 
 template <int ST>
-hipError_t launch_narrow_k(const InstDesc &t, int k, int src, int wpb, int remap, hipStream_t s) {
-    if (k == 2) return launch_narrow_t<ST, 2>(t, src, wpb, remap, s);
+hipError_t launch_narrow_k(const InstDesc &t, int k, int src, int wpb, int remap, int depth, hipStream_t s) {
+    if (k == 2) return launch_narrow_t<ST, 2>(t, src, wpb, remap, depth, s);
     if constexpr (ST != ST_F64)
-        if (k == 3) return launch_narrow_t<ST, 3>(t, src, wpb, remap, s);
+        if (k == 3) return launch_narrow_t<ST, 3>(t, src, wpb, remap, depth, s);
     return hipErrorInvalidValue;
 }
 
@@ -464,20 +529,27 @@ hipError_t launch_narrow_batch_k(const InstDesc *descs, int ndescs, const int4 *
     const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
     const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
     const int r = l.xcd_remap;
-    if (k == 2 && links)
-        narrow_batch_kernel<ST, 2, true><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
-    else if (k == 2)
-        narrow_batch_kernel<ST, 2, false><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
-    else if constexpr (ST != ST_F64) {
-        if (k != 3) return hipErrorInvalidValue;
+    const bool deep = narrow_depth(ST, nitems) == 2;
+    const auto launch = [&](auto kernel) {
+        kernel<<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+        return hipGetLastError();
+    };
+    if (k == 2) {
         if (links)
-            narrow_batch_kernel<ST, 3, true><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
-        else
-            narrow_batch_kernel<ST, 3, false><<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
-    } else {
-        return hipErrorInvalidValue;
+            return deep ? launch(narrow_batch_kernel<ST, 2, true, 2>)
+                        : launch(narrow_batch_kernel<ST, 2, true, 1>);
+        return deep ? launch(narrow_batch_kernel<ST, 2, false, 2>)
+                    : launch(narrow_batch_kernel<ST, 2, false, 1>);
     }
-    return hipGetLastError();
+    if constexpr (ST != ST_F64) {
+        if (k == 3 && links)
+            return deep ? launch(narrow_batch_kernel<ST, 3, true, 2>)
+                        : launch(narrow_batch_kernel<ST, 3, true, 1>);
+        if (k == 3)
+            return deep ? launch(narrow_batch_kernel<ST, 3, false, 2>)
+                        : launch(narrow_batch_kernel<ST, 3, false, 1>);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -501,9 +573,9 @@ hipError_t launch_narrow(const InstDesc &d, int storage, const NarrowPlan &p, in
     if (!narrow_eligible(d, storage)) return hipErrorInvalidValue;
     const InstDesc t = narrow_desc(d, p.k, p.rows);
     switch (storage) {
-        case ST_F64: return launch_narrow_k<ST_F64>(t, p.k, src, p.waves_per_block, p.remap, stream);
-        case ST_F32: return launch_narrow_k<ST_F32>(t, p.k, src, p.waves_per_block, p.remap, stream);
-        case ST_F16: return launch_narrow_k<ST_F16>(t, p.k, src, p.waves_per_block, p.remap, stream);
+        case ST_F64: return launch_narrow_k<ST_F64>(t, p.k, src, p.waves_per_block, p.remap, p.depth, stream);
+        case ST_F32: return launch_narrow_k<ST_F32>(t, p.k, src, p.waves_per_block, p.remap, p.depth, stream);
+        case ST_F16: return launch_narrow_k<ST_F16>(t, p.k, src, p.waves_per_block, p.remap, p.depth, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -538,17 +610,24 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     (three steps 8.2 there, but callers rely on two and eight rows as the
 //     default at that size), 1448^2 19.6 / 15.5 (three steps; two 20.1),
 //     2048^2 27.9 / 27.3; channel 1001 x 513 10.5 / 7.1.
-//   FP16: 128^2 7.5 / 3.2, 512^2 8.2 / 5.3, 1024^2 11.9 / 9.9, 2048^2 25.9 /
-//     27.3 (so not there); cylinder 1050^2 21.1 / 12.8; obstacle 2048^2 47.4 /
-//     34.7 (three steps 35.2).
+//   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
+//     14.9, 2048^2 25.9 / 27.3 (so not there); cylinder 1050^2 21.1 / 11.0;
+//     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
 // Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows, so R is the
 // smallest that leaves at most two wavefronts per SIMD (FP64: one) -- up to a
 // cap from where the launch is bound by memory rather than by latency and
 // shorter blocks in more rounds balance better (FP64 2048^2: 8 rows 70, 12
 // rows 71.5, 16 and up over 73 us; 182 VGPRs with links keep two wavefronts
 // per SIMD, 1050^2: 8 rows 26.3, 10 rows 20.4).
+// Loads two rows ahead: a lone wavefront's pipeline row (about 1 us) is shorter
+// than a load from memory, so one row ahead leaves it waiting -- two against
+// one: FP64 128^2 2.68 / 2.99, 512^2 5.71 / 6.00, cylinder 400 x 200 4.98 /
+// 5.50; FP32 128^2 2.37 / 2.73, 512^2 4.08 / 4.35, cylinder 4.31 / 4.63, channel
+// 6.79 / 6.97; FP16 128^2 2.47 / 3.19, 1024^2 9.26 / 10.1, 1448^2 14.9 / 16.0.
+// With more wavefronts per SIMD the registers cost more than it hides (FP64
+// 1024^2 18.95 / 18.06, FP32 1448^2 15.8 / 15.6), but for FP16.
 NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
-    const NarrowPlan p0 = {0, 0, 0, 0};
+    const NarrowPlan p0 = {0, 0, 0, 0, 1};
     NarrowPlan p = p0;
     const bool automatic = l.rows_per_wave == 0 && l.waves_per_block == 0 && l.cols_per_lane == 0 &&
                            l.steps_per_sweep == 0 && l.prefetch_rows == 0;
@@ -560,12 +639,13 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
     if (storage == ST_F32) {
         if (wide && nodes >= 2048 * 2048) return p0;
         if (nodes > (wide ? k1 * k1 : k1 * k1 / 2)) p.k = 3;
-    } else if (storage == ST_F16 && wide && nodes > k1 * k1 * 5 / 4) {
+    } else if (storage == ST_F16 && wide && nodes > k1 * k1 * 5 / 2) {
         return p0;
     }
     const int cap = narrow_cap(storage, p.k, d.links != nullptr, nodes);
     const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };
     p.rows = narrow_rows(storage, cap, waves);
+    p.depth = narrow_depth(storage, waves(p.rows));
     p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
     p.remap = l.remap_asked ? l.xcd_remap : 1;
     return p;

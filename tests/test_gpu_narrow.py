@@ -69,7 +69,7 @@ def test_equals_one_step_per_launch(L, kind, storage):
 @pytest.mark.parametrize("kind,storage,nx,ny,k", [
     ("open", "f32", 1300, 901, 3), ("obstacle", "f32", 1100, 600, 3), ("walls", "f32", 1300, 901, 3),
     ("cylinder", "f32", 1050, 700, 3), ("open", "f64", 700, 530, 2), ("cylinder", "f64", 900, 640, 2),
-    ("obstacle", "f16", 1500, 1100, 2), ("open", "f16", 900, 800, 2)])
+    ("obstacle", "f16", 1500, 1100, 2), ("open", "f16", 900, 800, 2), ("open", "f16", 1411, 1001, 2)])
 def test_larger_lattices_equal_one_step_per_launch(L, kind, storage, nx, ny, k):
     """The sizes from which the rule takes more steps, longer blocks and
     wider workgroups; steps that are not a multiple of the launch's."""
