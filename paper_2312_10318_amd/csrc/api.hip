@@ -1087,6 +1087,8 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
             wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
         nodes += (int64_t)d.nx * d.ny;
     }
+    // FP64: as one lattice of all the members' nodes would (narrow_plan)
+    if (automatic && b->storage == trt::ST_F64 && nodes > trt::kThreeStepNodesF64) b->k2 = 3;
     const bool small = wide_waves < (b->storage == trt::ST_F32 ? 8192 : 4096);
     b->cls.assign(n, kOneStep);
     b->multi = false;

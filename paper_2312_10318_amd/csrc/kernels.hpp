@@ -166,8 +166,9 @@ hipError_t launch_sweep_tb3_batch(const InstDesc *descs, int ndescs, const int4 
                                   hipStream_t stream);
 
 // Several time steps per launch with one column per lane (narrow.hip): any
-// storage, mask and boundary, k = 2, or 3 with FP32 or FP16 storage.  A
-// wavefront's window of 64 columns stores narrow_valid(k) of them.
+// storage, mask and boundary, k = 2 or 3.  A wavefront's window of 64 columns stores narrow_valid(k) of them.
+// FP64 lattices beyond this take three steps per launch, the others two
+constexpr int64_t kThreeStepNodesF64 = 3 * 1024 * 1024 / 8;
 constexpr int narrow_valid(int k) { return 64 - 2 * (2 * k - 1); }
 // fewer rows than this run fewer than a block's own rows of fill
 constexpr int kNarrowMinRows = 16;
@@ -186,14 +187,15 @@ inline int64_t narrow_waves(const InstDesc &d, int k, int r) {
 // The most rows per block, and the rows from the wavefronts that r rows give
 // (see narrow_plan).
 inline int narrow_cap(int storage, int k, bool links, int64_t nodes) {
-    if (storage == ST_F64) return links ? 10 : 8;
+    if (storage == ST_F64) return k == 2 ? (links ? 10 : 8) : (nodes > 3 * 1024 * 1024 ? 14 : 12);
     if (storage == ST_F32) return k == 2 ? 8 : 16;
     return nodes > 1024 * 1024 * 5 / 4 ? 12 : 5;
 }
 // Rows ahead of their use that a launch of `waves` wavefronts loads: two where
 // a wavefront is alone on its SIMD or nearly so, and FP16 always (see
-// narrow_plan).
-inline int narrow_depth(int storage, int64_t waves) {
+// narrow_plan); one for FP64's three steps.
+inline int narrow_depth(int storage, int k, int64_t waves) {
+    if (storage == ST_F64 && k == 3) return 1;
     return storage == ST_F16 || waves <= 2048 ? 2 : 1;
 }
 template <class W> int narrow_rows(int storage, int cap, W waves) {

@@ -46,25 +46,34 @@ template <> struct Pop<ST_F16> {
     __device__ static __forceinline__ W shl(W v) { return dpp_shl(0u, v); }
 };
 
-// One step's collided rows in flight: the row behind the fresh one (all nine
-// populations with LINK, whose nodes may take their own back; else 0, 1, 3 and
-// those streaming up, 2, 5, 6) and, of the row behind that, 2, 5, 6.
-template <int ST, bool LINK> struct Window {
+// FP64's three steps with a link map: bounced pulls of 2, 5, 6 are settled when
+// a row enters the window, from its nodes' own 4, 7, 8, which then need no
+// place in it (two wavefronts per SIMD and no spills; elsewhere the two looks
+// at the code cost more than the registers: a server quantum in FP16 4178
+// against 3766 us).
+template <int ST, int K, bool LINK> constexpr bool kSettle = LINK && ST == ST_F64 && K == 3;
+
+// One step's collided rows in flight: of the row behind the fresh one,
+// populations 0, 1, 3 and those streaming up, 2, 5, 6 -- with LINK all nine, as a
+// bounced pull takes a node's own back -- and the 2, 5, 6 of the row below it
+// (kSettle: as its pulls bring them).
+template <int ST, int K, bool LINK> struct Window {
     using W = typename Pop<ST>::W;
-    W lo[3];
-    W mid[LINK ? 9 : 6];
+    static constexpr bool kAll = LINK && !kSettle<ST, K, LINK>;
+    W in[3];
+    W mid[kAll ? 9 : 6];
+    // where population i sits in mid (-1: not kept)
+    __host__ __device__ static constexpr int at(int i) {
+        constexpr int six[9] = {0, 1, 3, 2, -1, 4, 5, -1, -1};
+        return kAll ? i : six[i];
+    }
 };
-// where population i sits in Window::mid (-1: not kept)
-template <bool LINK> __host__ __device__ constexpr int mid_of(int i) {
-    constexpr int at[9] = {0, 1, 3, 2, -1, 4, 5, -1, -1};
-    return LINK ? i : at[i];
-}
 
 template <int ST, int K, bool LINK> struct NarrowState {
     using C = typename Store<ST>::C;
     Coeffs<C> k[K];        // per step: the next row to collide,
     C py[K], below[K];     // its Phi_y and that of the row below it
-    Window<ST, LINK> w[K - 1];
+    Window<ST, K, LINK> w[K - 1];
     uint32_t code[K];      // LINK: half j of the whole: the code of row y + 2 K - 1 - j
     uint32_t flagged;      // LINK (uniform): bit j: that row has links in the window
 };
@@ -300,8 +309,9 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
                 c.out.st(i * c.plane + e0, c.col.oc, narrow_out<ST>(o[i]));
         }
     } else {
-        Window<ST, LINK> &w = s.w[Q];
-        constexpr auto at = mid_of<LINK>;
+        constexpr bool settle = kSettle<ST, K, LINK>;
+        Window<ST, K, LINK> &w = s.w[Q];
+        constexpr auto at = Window<ST, K, LINK>::at;
         Coeffs<C> next_k;
         C next_y = C(0);
         if (!FILL || stage > 2 * Q + 1) {
@@ -309,9 +319,9 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
             g[0] = w.mid[at(0)];
             g[1] = P::shr(w.mid[at(1)]);
             g[3] = P::shl(w.mid[at(3)]);
-            g[2] = w.lo[0];
-            g[5] = P::shr(w.lo[1]);
-            g[6] = P::shl(w.lo[2]);
+            g[2] = w.in[0];
+            g[5] = settle ? w.in[1] : P::shr(w.in[1]);
+            g[6] = settle ? w.in[2] : P::shl(w.in[2]);
             g[4] = o[4];
             g[7] = P::shl(o[7]);
             g[8] = P::shr(o[8]);
@@ -321,7 +331,8 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
                     code = s.code[Q + 1] & 0xffffu;
 #pragma unroll
                     for (int i = 1; i < 9; ++i)
-                        g[i] = ((code >> i) & 1u) ? w.mid[at(kOppDir[i])] : g[i];
+                        if (at(kOppDir[i]) >= 0)
+                            g[i] = ((code >> i) & 1u) ? w.mid[at(kOppDir[i])] : g[i];
                 }
             }
             C f[9];
@@ -329,9 +340,17 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
             for (int i = 0; i < 9; ++i) f[i] = P::widen(g[i]);
             next_y = narrow_coeffs<ST, LINK>(next_k, f, code, c, rt);
         }
-        w.lo[0] = w.mid[at(2)];
-        w.lo[1] = w.mid[at(5)];
-        w.lo[2] = w.mid[at(6)];
+        w.in[0] = w.mid[at(2)];
+        w.in[1] = settle ? P::shr(w.mid[at(5)]) : w.mid[at(5)];
+        w.in[2] = settle ? P::shl(w.mid[at(6)]) : w.mid[at(6)];
+        if constexpr (settle) {
+            if ((s.flagged >> (2 * Q + 1)) & 1u) {
+                const uint32_t code = s.code[Q] >> 16;
+                w.in[0] = ((code >> 2) & 1u) ? o[4] : w.in[0];
+                w.in[1] = ((code >> 5) & 1u) ? o[7] : w.in[1];
+                w.in[2] = ((code >> 6) & 1u) ? o[8] : w.in[2];
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             if (at(i) >= 0) w.mid[at(i)] = o[i];
@@ -362,11 +381,18 @@ __device__ __forceinline__ void narrow_row(NarrowState<ST, K, LINK> &s, NarrowRo
         for (int j = K - 1; j > 0; --j) s.code[j] = (s.code[j] << 16) | (s.code[j - 1] >> 16);
         s.code[0] = (s.code[0] << 16) | code;
     }
-    if (load) {
+    // FP64's three steps load after the first step's moments: its populations
+    // and the next ones would not fit beside the pipeline's state
+    constexpr bool late = ST == ST_F64 && K == 3;
+    if (!late && load) {
         q.take(row, c);
         narrow_load<ST, LINK>(row, c, yload);
     }
     const C py = narrow_coeffs<ST, LINK>(k, f, code, c, rt);
+    if (late && load) {
+        q.take(row, c);
+        narrow_load<ST, LINK>(row, c, yload);
+    }
     narrow_step<0, ST, K, LINK, FILL>(s, k, py, c, rt, y, stage);
 }
 
@@ -470,9 +496,16 @@ __device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int r
 }
 
 constexpr int kNarrowMaxWaves = 4;
+// Wavefronts per SIMD whose registers a variant is held to: FP64 two (three
+// steps would take a few more and leave one), FP32's three steps four (130
+// VGPRs otherwise, one too many rows of them for that).
+template <int ST, int K, bool LINK, int DEPTH>
+constexpr int kMinWaves = ST == ST_F64 ? 2 : (ST == ST_F32 && K == 3 && !LINK && DEPTH == 1 ? 4 : 1);
+// which combinations load two rows ahead (FP64's three steps would spill)
+template <int ST, int K> constexpr bool kDeep = !(ST == ST_F64 && K == 3);
 
 template <int ST, int K, bool LINK, int DEPTH>
-__global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(InstDesc d, int srcsel,
+__global__ __launch_bounds__(64 * kNarrowMaxWaves, (kMinWaves<ST, K, LINK, DEPTH>)) void narrow_kernel(InstDesc d, int srcsel,
                                                                      int remap) {
     int b = blockIdx.x;
     if (remap) b = xcd_remap(b, gridDim.x);
@@ -485,7 +518,7 @@ __global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_kernel(InstDesc d
 
 // Batched: wavefront w takes item w = (member, window, row block, -).
 template <int ST, int K, bool LINK, int DEPTH>
-__global__ __launch_bounds__(64 * kNarrowMaxWaves) void narrow_batch_kernel(
+__global__ __launch_bounds__(64 * kNarrowMaxWaves, (kMinWaves<ST, K, LINK, DEPTH>)) void narrow_batch_kernel(
     const InstDesc *__restrict__ descs, int ndescs, const int4 *__restrict__ items, int nitems,
     int flip, int remap) {
     int b = blockIdx.x;
@@ -503,52 +536,48 @@ template <int ST, int K>
 hipError_t launch_narrow_t(const InstDesc &t, int src, int wpb, int remap, int depth, hipStream_t s) {
     const int waves = t.strips * t.rowblocks;
     const int blocks = (waves + wpb - 1) / wpb;
-    if (depth == 2 && t.links)
-        narrow_kernel<ST, K, true, 2><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
-    else if (depth == 2)
-        narrow_kernel<ST, K, false, 2><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
-    else if (t.links)
-        narrow_kernel<ST, K, true, 1><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
-    else
-        narrow_kernel<ST, K, false, 1><<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
-    return hipGetLastError();
+    const auto launch = [&](auto kernel) {
+        kernel<<<blocks, 64 * wpb, 0, s>>>(t, src, remap);
+        return hipGetLastError();
+    };
+    if constexpr (kDeep<ST, K>)
+        if (depth == 2)
+            return t.links ? launch(narrow_kernel<ST, K, true, 2>)
+                           : launch(narrow_kernel<ST, K, false, 2>);
+    return t.links ? launch(narrow_kernel<ST, K, true, 1>) : launch(narrow_kernel<ST, K, false, 1>);
 }
 
 template <int ST>
 hipError_t launch_narrow_k(const InstDesc &t, int k, int src, int wpb, int remap, int depth, hipStream_t s) {
     if (k == 2) return launch_narrow_t<ST, 2>(t, src, wpb, remap, depth, s);
-    if constexpr (ST != ST_F64)
-        if (k == 3) return launch_narrow_t<ST, 3>(t, src, wpb, remap, depth, s);
+    if (k == 3) return launch_narrow_t<ST, 3>(t, src, wpb, remap, depth, s);
     return hipErrorInvalidValue;
+}
+
+template <int ST, int K>
+hipError_t launch_narrow_batch_t(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
+                                 bool links, int flip, const Launch &l, hipStream_t s) {
+    // one-wavefront workgroups while they spread over the CUs at once
+    const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
+    const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
+    const int r = l.xcd_remap;
+    const auto launch = [&](auto kernel) {
+        kernel<<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
+        return hipGetLastError();
+    };
+    if constexpr (kDeep<ST, K>)
+        if (narrow_depth(ST, K, nitems) == 2)
+            return links ? launch(narrow_batch_kernel<ST, K, true, 2>)
+                         : launch(narrow_batch_kernel<ST, K, false, 2>);
+    return links ? launch(narrow_batch_kernel<ST, K, true, 1>)
+                 : launch(narrow_batch_kernel<ST, K, false, 1>);
 }
 
 template <int ST>
 hipError_t launch_narrow_batch_k(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
                                  int k, bool links, int flip, const Launch &l, hipStream_t s) {
-    // one-wavefront workgroups while they spread over the CUs at once
-    const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
-    const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
-    const int r = l.xcd_remap;
-    const bool deep = narrow_depth(ST, nitems) == 2;
-    const auto launch = [&](auto kernel) {
-        kernel<<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
-        return hipGetLastError();
-    };
-    if (k == 2) {
-        if (links)
-            return deep ? launch(narrow_batch_kernel<ST, 2, true, 2>)
-                        : launch(narrow_batch_kernel<ST, 2, true, 1>);
-        return deep ? launch(narrow_batch_kernel<ST, 2, false, 2>)
-                    : launch(narrow_batch_kernel<ST, 2, false, 1>);
-    }
-    if constexpr (ST != ST_F64) {
-        if (k == 3 && links)
-            return deep ? launch(narrow_batch_kernel<ST, 3, true, 2>)
-                        : launch(narrow_batch_kernel<ST, 3, true, 1>);
-        if (k == 3)
-            return deep ? launch(narrow_batch_kernel<ST, 3, false, 2>)
-                        : launch(narrow_batch_kernel<ST, 3, false, 1>);
-    }
+    if (k == 2) return launch_narrow_batch_t<ST, 2>(descs, ndescs, items, nitems, links, flip, l, s);
+    if (k == 3) return launch_narrow_batch_t<ST, 3>(descs, ndescs, items, nitems, links, flip, l, s);
     return hipErrorInvalidValue;
 }
 
@@ -597,10 +626,11 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 // sets one asks for the passes those fields describe.  Measured on one box, us
 // per step, the other passes' default against this one's best shape and,
 // where it differs, the shape chosen here:
-//   FP64 (two steps; one per launch before): 128^2 6.6 / 3.1, 256^2 7.6 / 3.7,
-//     512^2 13.0 / 6.0, 1024^2 33.5 / 18.0, 2048^2 112 / 70, 4096^2 408 / 271;
-//     cylinder 400 x 200 14.5 / 5.7, 1050^2 43.8 / 20.4; channel 1000^2
-//     32.2 / 18.2.
+//   FP64 (one step per launch before): two steps 128^2 6.6 / 2.7, 256^2 7.6 /
+//     3.4, 512^2 13.0 / 5.7 (three 6.0), cylinder 400 x 200 14.5 / 5.0 (three
+//     6.2); three steps 724^2 7.9 (two 9.9), 1024^2 33.5 / 13.3 (18.2), 2048^2
+//     112 / 48.7 (70.5), 4096^2 408 / 186 (271), cylinder 724^2 11.7 (12.1),
+//     1050^2 43.8 / 18.0 (20.6), 2048^2 55 (71).
 //   FP32, any link map but whole-row walls (one step before): cylinder
 //     400 x 200 two steps 4.7, three 5.5 against 12.6; 1050^2 13.5 / 12.6
 //     against 26.4; obstacle 2048^2 38.0 / 31.2 against 68.6 -- three steps
@@ -616,9 +646,8 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 // Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows, so R is the
 // smallest that leaves at most two wavefronts per SIMD (FP64: one) -- up to a
 // cap from where the launch is bound by memory rather than by latency and
-// shorter blocks in more rounds balance better (FP64 2048^2: 8 rows 70, 12
-// rows 71.5, 16 and up over 73 us; 182 VGPRs with links keep two wavefronts
-// per SIMD, 1050^2: 8 rows 26.3, 10 rows 20.4).
+// shorter blocks in more rounds balance better (FP64 2048^2, three steps: 10
+// rows 50.4, 14 rows 48.7, 16 to 64 rows 50 and more).
 // Loads two rows ahead: a lone wavefront's pipeline row (about 1 us) is shorter
 // than a load from memory, so one row ahead leaves it waiting -- two against
 // one: FP64 128^2 2.68 / 2.99, 512^2 5.71 / 6.00, cylinder 400 x 200 4.98 /
@@ -636,18 +665,23 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
     const bool wide = tb2_eligible(d, storage);  // the 128-column passes apply
     constexpr int64_t k1 = 1024;
     p.k = 2;
-    if (storage == ST_F32) {
+    if (storage == ST_F64) {
+        if (nodes > kThreeStepNodesF64) p.k = 3;
+    } else if (storage == ST_F32) {
         if (wide && nodes >= 2048 * 2048) return p0;
         if (nodes > (wide ? k1 * k1 : k1 * k1 / 2)) p.k = 3;
-    } else if (storage == ST_F16 && wide && nodes > k1 * k1 * 5 / 2) {
+    } else if (wide && nodes > k1 * k1 * 5 / 2) {
         return p0;
     }
     const int cap = narrow_cap(storage, p.k, d.links != nullptr, nodes);
     const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };
     p.rows = narrow_rows(storage, cap, waves);
-    p.depth = narrow_depth(storage, waves(p.rows));
+    p.depth = narrow_depth(storage, p.k, waves(p.rows));
     p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
-    p.remap = l.remap_asked ? l.xcd_remap : 1;
+    // XCD bands, but for the large launches of FP64's three steps (2048^2 at 14
+    // rows 48.7 in round-robin order, 49.4 in bands)
+    const bool spread = storage == ST_F64 && p.k == 3 && p.waves_per_block == 4;
+    p.remap = l.remap_asked ? l.xcd_remap : (spread ? 0 : 1);
     return p;
 }
 
