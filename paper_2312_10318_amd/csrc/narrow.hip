@@ -34,16 +34,16 @@ namespace {
 template <int ST> struct Pop {
     using W = typename Store<ST>::C;
     __device__ static __forceinline__ W widen(W v) { return v; }
-    __device__ static __forceinline__ W shr(W v) { return dpp_shr(W(0), v); }
-    __device__ static __forceinline__ W shl(W v) { return dpp_shl(W(0), v); }
+    __device__ static __forceinline__ W shr(W v) { return dpp_shr0(v); }
+    __device__ static __forceinline__ W shl(W v) { return dpp_shl0(v); }
 };
 template <> struct Pop<ST_F16> {
     using W = uint32_t;
     __device__ static __forceinline__ float widen(W v) {
         return (float)__builtin_bit_cast(_Float16, (unsigned short)(v & 0xffffu));
     }
-    __device__ static __forceinline__ W shr(W v) { return dpp_shr(0u, v); }
-    __device__ static __forceinline__ W shl(W v) { return dpp_shl(0u, v); }
+    __device__ static __forceinline__ W shr(W v) { return dpp_shr0(v); }
+    __device__ static __forceinline__ W shl(W v) { return dpp_shl0(v); }
 };
 
 // FP64's three steps with a link map: bounced pulls of 2, 5, 6 are settled when
@@ -226,7 +226,7 @@ __device__ __forceinline__ typename Store<ST>::C narrow_coeffs(
     const C px = m.rho * m.ux * m.ux * m.ux;
     const C py = m.rho * m.uy * m.uy * m.uy;
     const C phix = solid ? C(0) : px;
-    C left = dpp_shr(C(0), phix), right = dpp_shl(C(0), phix);
+    C left = dpp_shr0(phix), right = dpp_shl0(phix);
     if (LINK && c.bounds) {
         // Phi beyond the inflow wall is the wall's; beyond the outlet, the
         // last column's

@@ -1154,31 +1154,31 @@ __device__ __forceinline__ void pull_coeffs_pair(Coeffs<C> &ckA, Coeffs<C> &ckB,
     C lf[9], rf[9];
     // node A: x - 1 is the previous lane's node B (it gives 1 and the
     // x + 1 movers of the other two rows: 5 and 8)
-    lw.mid[1] = dpp_shr(C(0), wB.mid[1]);
+    lw.mid[1] = dpp_shr0(wB.mid[1]);
     if (UP) {
-        lw.lo[1] = dpp_shr(C(0), wB.lo[1]);
-        lf[8] = dpp_shr(C(0), ob[8]);
+        lw.lo[1] = dpp_shr0(wB.lo[1]);
+        lf[8] = dpp_shr0(ob[8]);
     } else {
-        lw.lo[2] = dpp_shr(C(0), wB.lo[2]);
-        lf[5] = dpp_shr(C(0), ob[5]);
+        lw.lo[2] = dpp_shr0(wB.lo[2]);
+        lf[5] = dpp_shr0(ob[5]);
     }
     const bool behind = (wf & 2u) != 0, ahead = (wf & 4u) != 0, solid = (wf & 1u) != 0;
     mid_pull<C, UP, WALLS>(fa, wA, oa, lw, lf, wB, ob, behind, ahead);
     // node B: x + 2 is the next lane's node A (3, 6 and 7)
-    rw.mid[2] = dpp_shl(C(0), wA.mid[2]);
+    rw.mid[2] = dpp_shl0(wA.mid[2]);
     if (UP) {
-        rw.lo[2] = dpp_shl(C(0), wA.lo[2]);
-        rf[7] = dpp_shl(C(0), oa[7]);
+        rw.lo[2] = dpp_shl0(wA.lo[2]);
+        rf[7] = dpp_shl0(oa[7]);
     } else {
-        rw.lo[1] = dpp_shl(C(0), wA.lo[1]);
-        rf[6] = dpp_shl(C(0), oa[6]);
+        rw.lo[1] = dpp_shl0(wA.lo[1]);
+        rf[6] = dpp_shl0(oa[6]);
     }
     mid_pull<C, UP, WALLS>(fb, wB, ob, wA, oa, rw, rf, behind, ahead);
     RowState<C, SH> cA, cB;
     node_state<C, SH>(cA, fa, gx, gy, WALLS && solid);
     node_state<C, SH>(cB, fb, gx, gy, WALLS && solid);
-    const C left = dpp_shr(C(0), cB.phix);
-    const C right = dpp_shl(C(0), cA.phix);
+    const C left = dpp_shr0(cB.phix);
+    const C right = dpp_shl0(cA.phix);
     ckA = collide_coeffs<C, SH>(cA.m, C(0.5) * (cB.phix - left), w1, w2, ph, gx, gy);
     ckB = collide_coeffs<C, SH>(cB.m, C(0.5) * (right - cA.phix), w1, w2, ph, gx, gy);
     cyA = cA.phiy;
@@ -1212,8 +1212,8 @@ __device__ __forceinline__ void tb2_row(Tb2Carry<C> &k, PairRow<T> &raw, const P
         RowState<C, SH> nA, nB;
         widen_pair<T, C, SH, false, WALLS>(nA, nB, raw, cx, gx, gy, ox);
         if (load) tb2_gather<T, WALLS>(raw, cx, ln, odd, yload, lflags);
-        const C left = dpp_shr(C(0), nB.phix);
-        const C right = dpp_shl(C(0), nA.phix);
+        const C left = dpp_shr0(nB.phix);
+        const C right = dpp_shl0(nA.phix);
         nkA = collide_coeffs<C, SH>(nA.m, C(0.5) * (nB.phix - left), w1, w2, ph, gx, gy);
         nkB = collide_coeffs<C, SH>(nB.m, C(0.5) * (right - nA.phix), w1, w2, ph, gx, gy);
         nyA = nA.phiy;
@@ -1339,8 +1339,8 @@ __device__ __forceinline__ void tb2_row_h(K &k, PairRow<_Float16> &raw,
         RowState<C, SH> nA, nB;
         widen_pair<_Float16, C, SH, true, WALLS>(nA, nB, raw, cx, gx, gy, ox);
         if (load) tb2_gather<_Float16, WALLS>(raw, cx, ln, odd, yload, lflags);
-        const C left = dpp_shr(C(0), nB.phix);
-        const C right = dpp_shl(C(0), nA.phix);
+        const C left = dpp_shr0(nB.phix);
+        const C right = dpp_shl0(nA.phix);
         nkA = collide_coeffs<C, SH>(nA.m, C(0.5) * (nB.phix - left), w1, w2, ph, gx, gy);
         nkB = collide_coeffs<C, SH>(nB.m, C(0.5) * (right - nA.phix), w1, w2, ph, gx, gy);
         nyA = nA.phiy;
@@ -1395,8 +1395,8 @@ __device__ __forceinline__ void tb2_row_h(K &k, PairRow<_Float16> &raw,
         }
         RowState<C, SH> cA, cB;
         widen_pair<_Float16, C, SH, true, WALLS>(cA, cB, pr, cx, gx, gy, ox);
-        const C left = dpp_shr(C(0), cB.phix);
-        const C right = dpp_shl(C(0), cA.phix);
+        const C left = dpp_shr0(cB.phix);
+        const C right = dpp_shl0(cA.phix);
         ckA = collide_coeffs<C, SH>(cA.m, C(0.5) * (cB.phix - left), w1, w2, ph, gx, gy);
         ckB = collide_coeffs<C, SH>(cB.m, C(0.5) * (right - cA.phix), w1, w2, ph, gx, gy);
         cyA = cA.phiy;
@@ -1657,8 +1657,8 @@ __device__ __forceinline__ void tb3_row(Tb3Carry<float> &k, PairRow<float> &raw,
         RowState<C, SH> nA, nB;
         widen_pair<float, C, SH, false, WALLS>(nA, nB, raw, cx, gx, gy, ox);
         if (load) tb2_gather<float, WALLS>(raw, cx, ln, odd, yload, lflags);
-        const C left = dpp_shr(C(0), nB.phix);
-        const C right = dpp_shl(C(0), nA.phix);
+        const C left = dpp_shr0(nB.phix);
+        const C right = dpp_shl0(nA.phix);
         nkA = collide_coeffs<C, SH>(nA.m, C(0.5) * (nB.phix - left), w1, w2, ph, gx, gy);
         nkB = collide_coeffs<C, SH>(nB.m, C(0.5) * (right - nA.phix), w1, w2, ph, gx, gy);
         nyA = nA.phiy;

@@ -68,6 +68,35 @@ __device__ __forceinline__ double dpp_shl(double old, double src) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// The same shifts with zero in the lane that has no source: without a value to
+// keep, the destination needs no move ahead of the shift (two per double), and
+// the shift can become an operand modifier of its one use (a row of the
+// three-step FP64 pipeline: 445 -> 409 vector instructions).  100 steps of a
+// 1050^2 FP64 creeping flow with its tests 1.97 -> 1.92 ms, 4096^2 FP32 9.65 ->
+// 9.47 ms; lanes without a source feed no stored column either way.
+__device__ __forceinline__ uint32_t dpp_shr0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t dpp_shl0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float dpp_shr0(float v) {
+    return __builtin_bit_cast(float, dpp_shr0(__builtin_bit_cast(uint32_t, v)));
+}
+__device__ __forceinline__ float dpp_shl0(float v) {
+    return __builtin_bit_cast(float, dpp_shl0(__builtin_bit_cast(uint32_t, v)));
+}
+__device__ __forceinline__ double dpp_shr0(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, ((uint64_t)dpp_shr0((uint32_t)(b >> 32)) << 32) |
+                                          dpp_shr0((uint32_t)b));
+}
+__device__ __forceinline__ double dpp_shl0(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, ((uint64_t)dpp_shl0((uint32_t)(b >> 32)) << 32) |
+                                          dpp_shl0((uint32_t)b));
+}
+
 // A wave-uniform value in scalar registers.
 __device__ __forceinline__ float uniform(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
