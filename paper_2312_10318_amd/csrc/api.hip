@@ -963,22 +963,30 @@ static void batch_wide_items(trt_batch *b, const std::vector<size_t> &mem,
     const int valid2 = b->k2 == 3 ? trt::kTb3Valid : trt::kTb2Valid;
     Launch l2 = b->launch;
     if (l2.rows_per_wave <= 0) {
-        static const int kRows2[] = {32, 24, 16, 12, 8};
-        static const int kRows3[] = {32, 24, 20, 16, 12, 8};
-        const int *rows = b->k2 == 3 ? kRows3 : kRows2;
-        const int nrows = b->k2 == 3 ? 6 : 5;
-        const long long target = b->k2 == 3 ? 24576 : 32768;
-        l2.rows_per_wave = 8;
-        for (int i = 0; i < nrows; ++i) {
-            const int r = rows[i];
-            long long c = 0;
+        const auto windows = [&](int r) {
+            int64_t c = 0;
             for (size_t k : mem)
-                c += (long long)((descs[k].nx + valid2 - 1) / valid2) *
-                     ((descs[k].ny + r - 1) / r);
-            if (c >= target) {
-                l2.rows_per_wave = r;
-                break;
+                c += (int64_t)((descs[k].nx + valid2 - 1) / valid2) * ((descs[k].ny + r - 1) / r);
+            return c;
+        };
+        if (b->k2 == 3) {
+            // Two wavefronts fit a SIMD: the rounds of 2048 wavefronts times
+            // what a block runs, its rows and about five rows' worth of fill.
+            int64_t least = INT64_MAX;
+            for (int r : {8, 12, 16, 20, 24}) {
+                const int64_t c = (windows(r) + 2047) / 2048 * (r + 5);
+                if (c < least) {
+                    least = c;
+                    l2.rows_per_wave = r;
+                }
             }
+        } else {
+            l2.rows_per_wave = 8;
+            for (int r : {32, 24, 16, 12})
+                if (windows(r) >= 32768) {
+                    l2.rows_per_wave = r;
+                    break;
+                }
         }
     }
     const size_t from = items.size();
@@ -1074,22 +1082,29 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // take (FP64, link maps other than whole-row walls) are narrow, two steps
     // per launch (FP32: as the wide members); and so are all members of a
     // batch too small for 128-column windows, by their number in blocks of 8
-    // rows (us per step, wide / narrow: FP32 93 windows 9.5 / 3.9, 1163 15.6 /
-    // 10.2, 3373 28.9 / 25.6, 4826 37.1 / 34.2, the 48-member sweep of 12 M nodes
-    // 104.4 / 107.6; FP16 93 9.9 / 4.3, 1163 15.2 / 11.8, 3373 26.5 / 23.2, 4826
-    // 31.3 / 31.9).
+    // rows (us per step, wide / narrow: FP32 93 windows 9.5 / 3.9, 1593 15.9 /
+    // 12.1, 2567 21.4 / 19.0, 3553 25.6 / 24.3, 4163 29.0 / 30.5, 4927 33.1 /
+    // 34.4, 5982 36.8 / 39.3; FP16 93 9.9 / 4.3, 1163 15.2 / 11.8, 3373 26.5 /
+    // 23.2, 4826 31.3 / 31.9); in FP32 also of twice that many where narrow
+    // windows cover the members with a twentieth fewer lanes (5733 windows over
+    // 240 members of 64^2 to 200^2, 8% fewer: 38.8 / 32.0).
     const int sps = b->launch.steps_per_sweep;
     const bool automatic = sps == 0 && b->launch.rows_per_wave == 0;
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
-    int64_t wide_waves = 0, nodes = 0;
+    int64_t wide_waves = 0, wide_lanes = 0, narrow_lanes = 0, nodes = 0;
     for (const InstDesc &d : descs) {
-        if (trt::tb2_eligible(d, b->storage) && !resident_size(d))
+        if (trt::tb2_eligible(d, b->storage) && !resident_size(d)) {
+            const int valid = trt::narrow_valid(b->k2);
             wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
+            wide_lanes += (int64_t)(d.nx + trt::kTb3Valid - 1) / trt::kTb3Valid * 128 * d.ny;
+            narrow_lanes += (int64_t)(d.nx + valid - 1) / valid * 64 * d.ny;
+        }
         nodes += (int64_t)d.nx * d.ny;
     }
     // FP64: as one lattice of all the members' nodes would (narrow_plan)
     if (automatic && b->storage == trt::ST_F64 && nodes > trt::kThreeStepNodesF64) b->k2 = 3;
-    const bool small = wide_waves < (b->storage == trt::ST_F32 ? 8192 : 4096);
+    const bool small = wide_waves < 4096 || (b->storage == trt::ST_F32 && wide_waves < 8192 &&
+                                             20 * narrow_lanes < 19 * wide_lanes);
     b->cls.assign(n, kOneStep);
     b->multi = false;
     for (size_t k = 0; k < n; ++k) {
@@ -1140,10 +1155,15 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // items to balance.  Two steps: the longest of 32, 24, 16, 12, 8 rows
     // that gives 32768 items (256 members of 64^2 ... 1024^2, 4-wavefront
     // workgroups: FP32 (loads two rows ahead) 112.5 / 116.5 / 118.1 GLUPS at
-    // 24 / 16 / 12 rows, FP16 (one row ahead) 163.5 / 169.9 / 173.3).  Three
-    // steps (ten rows of fill per block): the longest of 32, 24, 20, 16, 12,
-    // 8 that gives 24576 items (FP32 152.7 / 154.5 / 155.4 / 153.8 / 147.2
-    // GLUPS at 32 / 24 / 20 / 16 / 12 rows).  Else 8.), then their items
+    // 24 / 16 / 12 rows, FP16 (one row ahead) 163.5 / 169.9 / 173.3), else 8.
+    // Three steps: the rows of 8 to 24 whose rounds of wavefronts are the
+    // cheapest.  8 rows, which any batch below 24576 items took, read their 14
+    // rows of halo as well, 2.8 times the lattice from memory on 48 members of
+    // 12 M nodes.  us per step at 8 / 12 / 16 / 20 / 24 rows (chosen: *):
+    // 16 members, 4.3 M nodes 35.5 / 34.8 / 37.6 / *31.0 / 33.6 (2048 items at
+    // 20); 30, 5.2 M 40.5 / 37.9 / 40.8 / 45.6 / *36.8 (2042 at 24); 48, 7.5 M
+    // 58.7 / 54.3 / 56.3 / *54.9 / 59.1; 96, 22 M 161 / 151.4 / 148.6 / 151.9 /
+    // *151.5; 300, 62 M 435 / 399 / 392 / *393 / 396), then their items
     std::vector<size_t> mem, narrow;
     for (size_t k = 0; k < n; ++k) {
         if (b->cls[k] == kWide) mem.push_back(k);
