@@ -1014,8 +1014,7 @@ static void batch_narrow_items(trt_batch *b, const std::vector<size_t> &mem, int
                                Order order) {
     bool links = false;
     for (size_t k : mem) links = links || descs[k].links != nullptr;
-    const int cap = trt::narrow_cap(b->storage, b->k2, links, nodes);
-    const int rows = trt::narrow_rows(b->storage, cap, [&](int r) {
+    const int rows = trt::narrow_rows(b->storage, b->k2, links, nodes, [&](int r) {
         int64_t w = 0;
         for (size_t k : mem) w += trt::narrow_waves(descs[k], b->k2, r);
         return w;

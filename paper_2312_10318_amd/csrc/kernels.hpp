@@ -184,13 +184,6 @@ InstDesc narrow_desc(const InstDesc &d, int k, int rows);
 inline int64_t narrow_waves(const InstDesc &d, int k, int r) {
     return (int64_t)((d.nx + narrow_valid(k) - 1) / narrow_valid(k)) * ((d.ny + r - 1) / r);
 }
-// The most rows per block, and the rows from the wavefronts that r rows give
-// (see narrow_plan).
-inline int narrow_cap(int storage, int k, bool links, int64_t nodes) {
-    if (storage == ST_F64) return k == 2 ? (links ? 10 : 8) : (nodes > 3 * 1024 * 1024 ? 14 : 12);
-    if (storage == ST_F32) return k == 2 ? 8 : 16;
-    return nodes > 1024 * 1024 * 5 / 4 ? 12 : 5;
-}
 // Rows ahead of their use that a launch of `waves` wavefronts loads: two where
 // a wavefront is alone on its SIMD or nearly so, and FP16 always (see
 // narrow_plan); one for FP64's three steps.
@@ -198,12 +191,35 @@ inline int narrow_depth(int storage, int k, int64_t waves) {
     if (storage == ST_F64 && k == 3) return 1;
     return storage == ST_F16 || waves <= 2048 ? 2 : 1;
 }
-template <class W> int narrow_rows(int storage, int cap, W waves) {
-    const int64_t most = storage == ST_F64 ? 1024 : 2048;
-    // a single row per block only while that leaves one wavefront per SIMD
-    int r = waves(1) <= 1024 ? 1 : 2;
-    while (r < cap && waves(r) > most) ++r;
-    return r;
+// Rows per block, from waves(r), the wavefronts that blocks of r rows give (the
+// reasons and figures: narrow_plan).
+template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes, W waves) {
+    if (storage == ST_F64 || (storage == ST_F32 && k == 2)) {
+        int cap = 8;
+        if (storage == ST_F64) cap = k == 2 ? (links ? 10 : 8) : (nodes > 3 * 1024 * 1024 ? 14 : 12);
+        const int64_t most = storage == ST_F64 ? 1024 : 2048;
+        // a single row per block only while that leaves one wavefront per SIMD
+        int r = waves(1) <= 1024 ? 1 : 2;
+        while (r < cap && waves(r) > most) ++r;
+        return r;
+    }
+    // the cheapest: a block's rows and `fill` more, times the rounds of `each`
+    // wavefronts per SIMD, where a round of m costs start + 2 m
+    struct Fit { int cap, fill, each, start; };
+    const Fit f = storage == ST_F32 ? Fit{14, 4, 3, 2} : links ? Fit{9, 2, 2, 6} : Fit{9, 1, 5, 1};
+    const int64_t alone = storage == ST_F16 && links ? 2048 : 1024;
+    int best = 0;
+    int64_t least = 0;
+    for (int r = waves(1) <= alone ? 1 : 2; r <= f.cap; ++r) {
+        const int64_t n = (waves(r) + 1023) / 1024, m = n % f.each;
+        const int64_t c =
+            (r + f.fill) * (n / f.each * (f.start + 2 * f.each) + (m ? f.start + 2 * m : 0));
+        if (best == 0 || c < least) {
+            best = r;
+            least = c;
+        }
+    }
+    return best;
 }
 // k steps of the batch members named by items, as launch_sweep_tb2_batch
 // (descs tiled by narrow_desc; the members with a link map and those without

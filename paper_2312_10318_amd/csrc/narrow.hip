@@ -643,11 +643,18 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
 //     14.9, 2048^2 25.9 / 27.3 (so not there); cylinder 1050^2 21.1 / 11.0;
 //     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
-// Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows, so R is the
-// smallest that leaves at most two wavefronts per SIMD (FP64: one) -- up to a
-// cap from where the launch is bound by memory rather than by latency and
-// shorter blocks in more rounds balance better (FP64 2048^2, three steps: 10
-// rows 50.4, 14 rows 48.7, 16 to 64 rows 50 and more).
+// Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows.  FP64, and two
+// steps in FP32: the smallest R that leaves at most two wavefronts per SIMD
+// (FP64: one) -- up to a cap from where the launch is bound by memory rather
+// than by latency and shorter blocks in more rounds balance better (FP64
+// 2048^2, three steps: 10 rows 50.4, 14 rows 48.7, 16 to 64 rows 50 and more).
+// FP16, and three steps in FP32: the cheapest R by rounds of wavefronts, with
+// constants fitted to twelve sets of lattices from 300^2 to 2000^2, with and
+// without obstacles, at 15 rows each: within 2% of the best rows on average,
+// where the other rule's caps (16, and 5 or 12 rows) were 4 to 8% off.
+// Before / now: FP16 twelve channels and cylinders of 2.3 M nodes 21.9 / 19.3,
+// 1400^2 16.6 / 14.5, obstacles 17.6 / 16.3, cylinder 400 x 200 5.3 / 4.6; FP32
+// 2000^2 30.8 / 27.1, 12 obstacles of 500^2 30.5 / 24.6, 3 of 1100^2 28.5 / 26.2.
 // Loads two rows ahead: a lone wavefront's pipeline row (about 1 us) is shorter
 // than a load from memory, so one row ahead leaves it waiting -- two against
 // one: FP64 128^2 2.68 / 2.99, 512^2 5.71 / 6.00, cylinder 400 x 200 4.98 /
@@ -673,9 +680,8 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
     } else if (wide && nodes > k1 * k1 * 5 / 2) {
         return p0;
     }
-    const int cap = narrow_cap(storage, p.k, d.links != nullptr, nodes);
     const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };
-    p.rows = narrow_rows(storage, cap, waves);
+    p.rows = narrow_rows(storage, p.k, d.links != nullptr, nodes, waves);
     p.depth = narrow_depth(storage, p.k, waves(p.rows));
     p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
     // XCD bands, but for the large launches of FP64's three steps (2048^2 at 14
