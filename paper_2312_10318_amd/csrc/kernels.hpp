@@ -194,7 +194,8 @@ inline int narrow_depth(int storage, int k, int64_t waves) {
 // Rows per block, from waves(r), the wavefronts that blocks of r rows give (the
 // reasons and figures: narrow_plan).
 template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes, W waves) {
-    if (storage == ST_F64 || (storage == ST_F32 && k == 2)) {
+    const bool far = nodes > 5 * 1024 * 1024 / 2;  // FP64 beyond the memory-side cache
+    if (storage == ST_F64 ? k == 2 || far : storage == ST_F32 && k == 2) {
         int cap = 8;
         if (storage == ST_F64) cap = k == 2 ? (links ? 10 : 8) : (nodes > 3 * 1024 * 1024 ? 14 : 12);
         const int64_t most = storage == ST_F64 ? 1024 : 2048;
@@ -206,7 +207,9 @@ template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes
     // the cheapest: a block's rows and `fill` more, times the rounds of `each`
     // wavefronts per SIMD, where a round of m costs start + 2 m
     struct Fit { int cap, fill, each, start; };
-    const Fit f = storage == ST_F32 ? Fit{14, 4, 3, 2} : links ? Fit{9, 2, 2, 6} : Fit{9, 1, 5, 1};
+    Fit f = links ? Fit{9, 2, 2, 6} : Fit{9, 1, 5, 1};
+    if (storage == ST_F64) f = Fit{24, 5, 2, links ? 2 : 0};
+    if (storage == ST_F32) f = Fit{14, 4, 3, 2};
     const int64_t alone = storage == ST_F16 && links ? 2048 : 1024;
     int best = 0;
     int64_t least = 0;

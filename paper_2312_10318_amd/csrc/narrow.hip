@@ -645,16 +645,19 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
 // Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows.  FP64, and two
 // steps in FP32: the smallest R that leaves at most two wavefronts per SIMD
-// (FP64: one) -- up to a cap from where the launch is bound by memory rather
+// (FP64, but for three steps of up to 2.6 M nodes: one) -- up to a cap from where the launch is bound by memory rather
 // than by latency and shorter blocks in more rounds balance better (FP64
 // 2048^2, three steps: 10 rows 50.4, 14 rows 48.7, 16 to 64 rows 50 and more).
-// FP16, and three steps in FP32: the cheapest R by rounds of wavefronts, with
+// FP16, three steps in FP32 and those FP64 ones: the cheapest R by rounds of wavefronts, with
 // constants fitted to twelve sets of lattices from 300^2 to 2000^2, with and
 // without obstacles, at 15 rows each: within 2% of the best rows on average,
 // where the other rule's caps (16, and 5 or 12 rows) were 4 to 8% off.
 // Before / now: FP16 twelve channels and cylinders of 2.3 M nodes 21.9 / 19.3,
 // 1400^2 16.6 / 14.5, obstacles 17.6 / 16.3, cylinder 400 x 200 5.3 / 4.6; FP32
-// 2000^2 30.8 / 27.1, 12 obstacles of 500^2 30.5 / 24.6, 3 of 1100^2 28.5 / 26.2.
+// 2000^2 30.8 / 27.1, 12 obstacles of 500^2 30.5 / 24.6, 3 of 1100^2 28.5 / 26.2;
+// FP64 1200^2 20.9 / 17.3, 1400^2 25.4 / 23.3, obstacles 23.3 / 18.4 and 26.5 /
+// 24.6, 3000 x 500 21.5 / 17.6, twelve lattices of 2.3 M nodes 34.5 / 31.9, with
+// obstacles 35.3 / 33.0.
 // Loads two rows ahead: a lone wavefront's pipeline row (about 1 us) is shorter
 // than a load from memory, so one row ahead leaves it waiting -- two against
 // one: FP64 128^2 2.68 / 2.99, 512^2 5.71 / 6.00, cylinder 400 x 200 4.98 /
