@@ -200,7 +200,8 @@ template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes
         if (storage == ST_F64) cap = k == 2 ? (links ? 10 : 8) : (nodes > 3 * 1024 * 1024 ? 14 : 12);
         const int64_t most = storage == ST_F64 ? 1024 : 2048;
         // a single row per block only while that leaves one wavefront per SIMD
-        int r = waves(1) <= 1024 ? 1 : 2;
+        // (FP32 with a link map: two)
+        int r = waves(1) <= (storage == ST_F32 && links ? 2048 : 1024) ? 1 : 2;
         while (r < cap && waves(r) > most) ++r;
         return r;
     }

@@ -632,14 +632,17 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     112 / 48.7 (70.5), 4096^2 408 / 186 (271), cylinder 724^2 11.7 (12.1),
 //     1050^2 43.8 / 18.0 (20.6), 2048^2 55 (71).
 //   FP32, any link map but whole-row walls (one step before): cylinder
-//     400 x 200 two steps 4.7, three 5.5 against 12.6; 1050^2 13.5 / 12.6
-//     against 26.4; obstacle 2048^2 38.0 / 31.2 against 68.6 -- three steps
-//     pay once the lattice leaves the L2s.
-//   FP32, open or whole-row walls (128-column windows before): 128^2 8.0 / 2.6,
-//     256^2 8.0 / 3.1, 512^2 8.6 / 4.2, 724^2 9.1 / 6.0, 1024^2 12.6 / 10.6
-//     (three steps 8.2 there, but callers rely on two and eight rows as the
-//     default at that size), 1448^2 19.6 / 15.5 (three steps; two 20.1),
-//     2048^2 27.9 / 27.3; channel 1001 x 513 10.5 / 7.1.
+//     400 x 200 two steps 4.2, three 5.5 against 12.6; 700^2 7.1 / 8.0, 760^2
+//     8.2 / 8.3, 900^2 9.9 / 9.8, 1050^2 13.5 / 12.6 against 26.4; obstacle
+//     2048^2 38.0 / 31.2 against 68.6.
+//   FP32, whole-row walls (128-column windows before): channel 700^2 two steps
+//     7.1, three 7.2, 1001 x 513 7.2 / 7.1 against 10.5, 850^2 9.3 / 8.1, 1000^2
+//     11.9 / 9.7.
+//   FP32, neither (128-column windows before): 128^2 8.0 / 2.6, 200^2 two steps
+//     2.9, three 3.0, 400 x 200 3.4 / 3.2, 420^2 4.4 / 4.0, 512^2 4.5 / 4.4
+//     against 8.6, 800^2 7.2 / 6.8, 1000^2 11.0 / 8.2, 1448^2 20.1 / 15.5 against
+//     19.6, 2048^2 27.3 against 27.9.  1024^2 alone keeps two steps and eight
+//     rows (10.6; 8.2 with three; 12.6 before): callers rely on that default.
 //   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
 //     14.9, 2048^2 25.9 / 27.3 (so not there); cylinder 1050^2 21.1 / 11.0;
 //     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
@@ -679,7 +682,9 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
         if (nodes > kThreeStepNodesF64) p.k = 3;
     } else if (storage == ST_F32) {
         if (wide && nodes >= 2048 * 2048) return p0;
-        if (nodes > (wide ? k1 * k1 : k1 * k1 / 2)) p.k = 3;
+        const bool two = d.links ? nodes <= k1 * k1 / 2
+                                 : nodes <= k1 * 64 || (d.nx == k1 && d.ny == k1);
+        p.k = two ? 2 : 3;
     } else if (wide && nodes > k1 * k1 * 5 / 2) {
         return p0;
     }
