@@ -403,26 +403,35 @@ template <class T> struct BufAccess {
     }
     __device__ __forceinline__ T ld(int64_t elem, uint32_t voff) const;
     __device__ __forceinline__ void st(int64_t elem, uint32_t voff, T v) const;
+    // the same from a wave-uniform byte offset
+    __device__ __forceinline__ T ldb(uint32_t soff, uint32_t voff) const;
+    __device__ __forceinline__ void stb(uint32_t soff, uint32_t voff, T v) const;
 };
-template <> __device__ __forceinline__ float BufAccess<float>::ld(int64_t e, uint32_t v) const {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, (uint32_t)(e * 4), 0));
+template <> __device__ __forceinline__ float BufAccess<float>::ldb(uint32_t s, uint32_t v) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
 }
-template <> __device__ __forceinline__ void BufAccess<float>::st(int64_t e, uint32_t v, float x) const {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, v, (uint32_t)(e * 4), TRT_STORE_CPOL);
+template <> __device__ __forceinline__ void BufAccess<float>::stb(uint32_t s, uint32_t v, float x) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, v, s, TRT_STORE_CPOL);
 }
-template <> __device__ __forceinline__ _Float16 BufAccess<_Float16>::ld(int64_t e, uint32_t v) const {
+template <> __device__ __forceinline__ _Float16 BufAccess<_Float16>::ldb(uint32_t s, uint32_t v) const {
     return __builtin_bit_cast(_Float16,
-                              (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, v, (uint32_t)(e * 2), 0));
+                              (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0));
 }
-template <> __device__ __forceinline__ void BufAccess<_Float16>::st(int64_t e, uint32_t v, _Float16 x) const {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x), r, v, (uint32_t)(e * 2), TRT_STORE_CPOL);
+template <> __device__ __forceinline__ void BufAccess<_Float16>::stb(uint32_t s, uint32_t v, _Float16 x) const {
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x), r, v, s, TRT_STORE_CPOL);
 }
-template <> __device__ __forceinline__ double BufAccess<double>::ld(int64_t e, uint32_t v) const {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, (uint32_t)(e * 8), 0));
+template <> __device__ __forceinline__ double BufAccess<double>::ldb(uint32_t s, uint32_t v) const {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
 }
-template <> __device__ __forceinline__ void BufAccess<double>::st(int64_t e, uint32_t v, double x) const {
+template <> __device__ __forceinline__ void BufAccess<double>::stb(uint32_t s, uint32_t v, double x) const {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, v, (uint32_t)(e * 8), TRT_STORE_CPOL);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, v, s, TRT_STORE_CPOL);
+}
+template <class T> __device__ __forceinline__ T BufAccess<T>::ld(int64_t e, uint32_t v) const {
+    return ldb((uint32_t)(e * sizeof(T)), v);
+}
+template <class T> __device__ __forceinline__ void BufAccess<T>::st(int64_t e, uint32_t v, T x) const {
+    stb((uint32_t)(e * sizeof(T)), v, x);
 }
 
 // Pointer access (any lattice size): wave-uniform element offset + lane

@@ -84,6 +84,17 @@ template <int ST, bool LINK> struct NarrowRow {
     uint32_t flagged;
 };
 
+// Whether a lane keeps the byte offsets of its pulls and populations in a row, so
+// that an access adds the row's alone: 15 registers for 80 scalar instructions
+// in two pipeline rows (FP32, two steps: 646 instructions -> 558).  A lone
+// wavefront issues one instruction in five to six cycles whatever its kind, so
+// that is time where few wavefronts run (us per step, before / now: FP32 300^2
+// 3.26 / 3.10, 1000^2 8.23 / 8.12; FP64 400 x 200 with an obstacle 5.04 / 4.76;
+// FP16 300^2 3.59 / 3.41); beside others the registers count (FP16 obstacles
+// 1400^2 16.2 / 18.9: three wavefronts per SIMD instead of four).
+template <int ST, bool LINK, int DEPTH>
+constexpr bool kFold = DEPTH == 2 && !(ST == ST_F16 && LINK);
+
 // The collision's constants.
 template <class C> struct Consts {
     C w1, w2, ph, gx, gy;
@@ -100,31 +111,41 @@ struct RowFlags {
 };
 
 // What a wavefront needs of its lattice.
-template <int ST, bool LINK> struct NarrowCtx {
+template <int ST, bool LINK, bool FOLD> struct NarrowCtx {
     using T = typename Store<ST>::T;
     using C = typename Store<ST>::C;
     BufAccess<T> in, out;
     LinkAccess la;
     Column col;
-    int64_t plane;
-    int pitch, ny, nx;
-    int64_t lpitch;
+    uint32_t plane;  // bytes between a row's populations,
+    uint32_t row;    // and between rows
+    uint32_t from[9], own[9];  // FOLD: byte offsets in a row of the lane's pulls and populations
+    int ny, nx;
+    uint32_t lpitch;
     const __attribute__((address_space(4))) uint32_t *sum;
     int nsum, s0, s1, s2;  // the summary entries that cover the window
     bool bounds;           // (uniform) the window holds a boundary column of open x
     bool store;
     OpenX<C> ox;
 
+    // byte offsets, by lane and by wavefront, of the pull and of the population i
+    // of the row at e
+    __device__ __forceinline__ uint32_t side(int i) const {
+        return i == 1 || i == 5 || i == 8 ? col.om : (i == 3 || i == 6 || i == 7 ? col.op : col.oc);
+    }
+    __device__ __forceinline__ uint32_t pull_lane(int i) const { return FOLD ? from[i] : side(i); }
+    __device__ __forceinline__ uint32_t own_lane(int i) const { return FOLD ? own[i] : col.oc; }
+    __device__ __forceinline__ uint32_t wave(int i, uint32_t e) const { return FOLD ? e : e + i * plane; }
     // row y's summary entries
     __device__ __forceinline__ RowFlags summary(int y) const {
         if constexpr (!LINK) return RowFlags{0u, 0u, 0u};
-        const int64_t r = (int64_t)y * nsum;
+        const uint32_t r = (uint32_t)y * (uint32_t)nsum;
         return RowFlags{sum[r + s0], sum[r + s1], sum[r + s2]};
     }
     // the codes of row y's nodes (0 where the row has no links)
     __device__ __forceinline__ uint32_t codes(int y, uint32_t flagged) const {
         if constexpr (!LINK) return 0u;
-        return flagged ? la.ld1((uint32_t)((int64_t)y * lpitch), (uint32_t)col.xc) : 0u;
+        return flagged ? la.ld1((uint32_t)y * lpitch, (uint32_t)col.xc) : 0u;
     }
 };
 
@@ -138,7 +159,7 @@ template <int ST, bool LINK, int DEPTH> struct LinkQueue {
     int row;  // the row `ahead` describes
 
     // from the first row to load
-    __device__ __forceinline__ void start(const NarrowCtx<ST, LINK> &c, int y) {
+    template <class Ctx> __device__ __forceinline__ void start(const Ctx &c, int y) {
         if constexpr (LINK) {
 #pragma unroll
             for (int i = 0; i < DEPTH; ++i) {
@@ -151,7 +172,8 @@ template <int ST, bool LINK, int DEPTH> struct LinkQueue {
         }
     }
     // the link data of the next row to load, into r
-    __device__ __forceinline__ void take(NarrowRow<ST, LINK> &r, const NarrowCtx<ST, LINK> &c) {
+    template <class Ctx>
+    __device__ __forceinline__ void take(NarrowRow<ST, LINK> &r, const Ctx &c) {
         if constexpr (LINK) {
             r.code = code[0];
             r.flagged = flagged[0];
@@ -169,53 +191,40 @@ template <int ST, bool LINK, int DEPTH> struct LinkQueue {
 };
 
 // Load the pulls of row y (row.code, row.flagged already hold the row's).
-template <int ST, bool LINK>
+template <int ST, bool LINK, bool FOLD>
 __device__ __forceinline__ void narrow_load(NarrowRow<ST, LINK> &row,
-                                            const NarrowCtx<ST, LINK> &c, int y) {
-    using T = typename Store<ST>::T;
-    constexpr uint32_t es = sizeof(T);
+                                            const NarrowCtx<ST, LINK, FOLD> &c, int y) {
     const int ym = (y == 0) ? c.ny - 1 : y - 1;
     const int yp = (y == c.ny - 1) ? 0 : y + 1;
-    const int64_t e0 = (int64_t)y * c.pitch, em = (int64_t)ym * c.pitch,
-                  ep = (int64_t)yp * c.pitch;
-    const int64_t from[9] = {e0,
-                             c.plane + e0,
-                             2 * c.plane + em,
-                             3 * c.plane + e0,
-                             4 * c.plane + ep,
-                             5 * c.plane + em,
-                             6 * c.plane + em,
-                             7 * c.plane + ep,
-                             8 * c.plane + ep};
-    const uint32_t oc = c.col.oc, om = c.col.om, op = c.col.op;
-    const uint32_t at[9] = {oc, om, oc, op, oc, om, op, op, om};
+    const uint32_t e0 = (uint32_t)y * c.row, em = (uint32_t)ym * c.row, ep = (uint32_t)yp * c.row;
+    const uint32_t at[9] = {e0, e0, em, e0, ep, em, em, ep, ep};
     if constexpr (!LINK) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ld(from[i], at[i]);
+        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ldb(c.wave(i, at[i]), c.pull_lane(i));
     } else {
         // whole byte offsets (the lattice is at most 4 GiB), so that a lane
         // can point at its own slot instead
         uint32_t off[9];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) off[i] = at[i] + (uint32_t)(from[i] * es);
+        for (int i = 0; i < 9; ++i) off[i] = c.pull_lane(i) + c.wave(i, at[i]);
         if (row.flagged) {
 #pragma unroll
             for (int i = 1; i < 9; ++i) {
-                const uint32_t own = oc + (uint32_t)((kOppDir[i] * c.plane + e0) * es);
+                const uint32_t own = c.own_lane(kOppDir[i]) + c.wave(kOppDir[i], e0);
                 off[i] = ((row.code >> i) & 1u) ? own : off[i];
             }
         }
 #pragma unroll
-        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ld(0, off[i]);
+        for (int i = 0; i < 9; ++i) row.v[i] = c.in.ldb(0, off[i]);
     }
 }
 
 // Moments, gradient of Phi_x and coefficients of a row from its nodes'
 // populations; returns Phi_y.
-template <int ST, bool LINK>
+template <int ST, bool LINK, bool FOLD>
 __device__ __forceinline__ typename Store<ST>::C narrow_coeffs(
     Coeffs<typename Store<ST>::C> &k, typename Store<ST>::C f[9], uint32_t code,
-    const NarrowCtx<ST, LINK> &c, const Consts<typename Store<ST>::C> &rt) {
+    const NarrowCtx<ST, LINK, FOLD> &c, const Consts<typename Store<ST>::C> &rt) {
     using C = typename Store<ST>::C;
     constexpr bool SH = Store<ST>::shifted;
     if (LINK && c.bounds)
@@ -276,11 +285,11 @@ __device__ __forceinline__ typename Store<ST>::T narrow_out(typename Pop<ST>::W 
 // next step pulls the row behind that one and forms its coefficients, or, in
 // the last step, the row is stored.  FILL: stage g < 2 K - 1 of the pipeline's
 // fill runs the first g of these collisions and pulls.
-template <int Q, int ST, int K, bool LINK, bool FILL>
+template <int Q, int ST, int K, bool LINK, bool FILL, bool FOLD>
 __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
                                             const Coeffs<typename Store<ST>::C> &fresh_k,
                                             typename Store<ST>::C fresh_y,
-                                            const NarrowCtx<ST, LINK> &c,
+                                            const NarrowCtx<ST, LINK, FOLD> &c,
                                             const Consts<typename Store<ST>::C> &rt, int y,
                                             int stage) {
     using C = typename Store<ST>::C;
@@ -303,10 +312,10 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
             }
         }
         if (c.store) {
-            const int64_t e0 = (int64_t)y * c.pitch;
+            const uint32_t e0 = (uint32_t)y * c.row;
 #pragma unroll
-            for (int i = 0; i < 9; ++i)
-                c.out.st(i * c.plane + e0, c.col.oc, narrow_out<ST>(o[i]));
+            for (int i = 0; i < 9; ++i) 
+                c.out.stb(c.wave(i, e0), c.own_lane(i), narrow_out<ST>(o[i]));
         }
     } else {
         constexpr bool settle = kSettle<ST, K, LINK>;
@@ -362,10 +371,10 @@ __device__ __forceinline__ void narrow_step(NarrowState<ST, K, LINK> &s,
 // One pipeline row y: the first step's coefficients of gathered row
 // y + 2 K - 1, whose registers then take the loads of row yload (when
 // `load`), and the later parts (narrow_step).
-template <int ST, int K, bool LINK, bool FILL, int DEPTH>
+template <int ST, int K, bool LINK, bool FILL, int DEPTH, bool FOLD>
 __device__ __forceinline__ void narrow_row(NarrowState<ST, K, LINK> &s, NarrowRow<ST, LINK> &row,
                                            LinkQueue<ST, LINK, DEPTH> &q,
-                                           const NarrowCtx<ST, LINK> &c,
+                                           const NarrowCtx<ST, LINK, FOLD> &c,
                                            const Consts<typename Store<ST>::C> &rt, int y,
                                            bool load, int yload, int stage) {
     using C = typename Store<ST>::C;
@@ -431,23 +440,30 @@ __device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int r
         s1 = b >> 6;
         s2 = a + 63 >= nx ? 0 : s0;
     }
-    const NarrowCtx<ST, LINK> c{BufAccess<T>(src, bytes),
-                                BufAccess<T>(dst, bytes),
-                                LinkAccess(d.links, (uint64_t)ny * (uint64_t)d.lpitch),
-                                col,
-                                d.plane,
-                                d.pitch,
-                                ny,
-                                nx,
-                                d.lpitch,
-                                (const __attribute__((address_space(4))) uint32_t *)d.rowsum,
-                                d.nsum,
-                                s0,
-                                s1,
-                                s2,
-                                bounds,
-                                store,
-                                ox};
+    NarrowCtx<ST, LINK, kFold<ST, LINK, DEPTH>> c{BufAccess<T>(src, bytes),
+                          BufAccess<T>(dst, bytes),
+                          LinkAccess(d.links, (uint64_t)ny * (uint64_t)d.lpitch),
+                          col,
+                          (uint32_t)(d.plane * sizeof(T)),
+                          (uint32_t)(d.pitch * sizeof(T)),
+                          {},
+                          {},
+                          ny,
+                          nx,
+                          (uint32_t)d.lpitch,
+                          (const __attribute__((address_space(4))) uint32_t *)d.rowsum,
+                          d.nsum,
+                          s0,
+                          s1,
+                          s2,
+                          bounds,
+                          store,
+                          ox};
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        c.from[i] = c.side(i) + i * c.plane;
+        c.own[i] = col.oc + i * c.plane;
+    }
     const int y0 = rb * d.rows;
     const int y1 = min(y0 + d.rows, ny);
     const auto wrap_row = [&](int v) { v %= ny; return v < 0 ? v + ny : v; };
@@ -497,10 +513,14 @@ __device__ __forceinline__ void narrow_strip(const InstDesc &d, int strip, int r
 
 constexpr int kNarrowMaxWaves = 4;
 // Wavefronts per SIMD whose registers a variant is held to: FP64 two (three
-// steps would take a few more and leave one), FP32's three steps four (130
-// VGPRs otherwise, one too many rows of them for that).
+// steps would take a few more and leave one), FP32's three steps and FP16's two
+// with a link map four (130 and 129 VGPRs otherwise, one too many rows of them
+// for that).
 template <int ST, int K, bool LINK, int DEPTH>
-constexpr int kMinWaves = ST == ST_F64 ? 2 : (ST == ST_F32 && K == 3 && !LINK && DEPTH == 1 ? 4 : 1);
+constexpr int kMinWaves = ST == ST_F64                                        ? 2
+                          : ST == ST_F32 && K == 3 && !LINK && DEPTH == 1     ? 4
+                          : ST == ST_F16 && K == 2 && LINK                    ? 4
+                                                                              : 1;
 // which combinations load two rows ahead (FP64's three steps would spill)
 template <int ST, int K> constexpr bool kDeep = !(ST == ST_F64 && K == 3);
 
