@@ -158,7 +158,9 @@ typedef struct {
     int32_t steps_per_sweep; /* time steps per launch: 1, 2 or 3 (0: automatic -- three for
                                 FP32 simulations of at least 2048^2 nodes that allow it, else
                                 two where allowed; in a batch three for FP32 members, two for
-                                FP16; and see above).  k steps per launch move each
+                                FP16; in the one-column pass, see above, three for FP64 from
+                                about 3.9e5 nodes and for FP32 from 65537, 524289 with a
+                                mask or open boundaries, else two).  k steps per launch move each
                                 population through HBM once per k steps and give the bits of
                                 k one-step sweeps.  Two apply to FP32 and FP16 simulations,
                                 alone or in a batch, without a mask or open boundaries, or
@@ -363,10 +365,13 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims);
 
 /* Advance every member nsteps steps (replays of captured graphs of batched
  * launches as for trt_step, plus at most a few plain launches).  With
- * the default steps_per_sweep, members that allow it (FP32 or FP16 without
- * a mask or open boundaries, or with walls that fill whole rows) advance
- * three (FP32) or two (FP16) steps per launch and the others by one-step
- * sweeps in the same graphs; every member gets the bits it gets alone. */
+ * an automatic launch shape every member of at least 16 rows within 4 GiB
+ * advances two or three steps per launch (FP32 three, FP16 two, FP64 three
+ * in batches of more than about 3.9e5 nodes, else two), members of at most
+ * 1024 nodes all the steps of the call in one launch; steps_per_sweep or
+ * rows_per_wave set, those that the passes of trt_tuning allow, and the others
+ * by one-step sweeps in the same graphs.  Every member gets the bits it gets
+ * alone. */
 trt_status trt_batch_step(trt_batch *b, int64_t nsteps);
 
 /* Diagnostics of every member into device out[n][TRT_NDIAG]. */
@@ -376,8 +381,8 @@ trt_status trt_batch_diagnostics(trt_batch *b, double *out);
 trt_status trt_batch_set_tuning(trt_batch *b, const trt_tuning *t);
 
 /* The batch's launch shape as set (0 where automatic); steps_per_sweep
- * reports 2 only if some member takes two-step launches, prefetch_rows the
- * two-step launches' rows ahead in effect (0 without such members).  EINVAL
+ * reports 2 or 3 only if some member takes launches of several steps,
+ * prefetch_rows those launches' rows ahead in effect (0 without such members).  EINVAL
  * for a NULL handle or out. */
 trt_status trt_batch_get_tuning(const trt_batch *b, trt_tuning *t);
 

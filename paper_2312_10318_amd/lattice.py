@@ -136,8 +136,8 @@ class Lattice:
 
     def tuning(self):
         """(rows per wavefront, wavefronts per workgroup, XCD remap, columns per
-        lane, longest captured graph, time steps per launch, rows the two-step
-        loads run ahead: 0 for one step per launch) in effect."""
+        lane, longest captured graph, time steps per launch, rows the loads of
+        several steps run ahead: 0 for one step per launch) in effect."""
         return capi.trt_get_tuning(self.handle)
 
     def init_equilibrium(self, rho, ux, uy, sync=True):
@@ -267,7 +267,7 @@ class Lattice:
 
 
 class Batch:
-    """Many independent lattices advanced together, one launch per step."""
+    """Many independent lattices advanced together by the same launches."""
 
     def __init__(self, lattices):
         if not lattices:
@@ -289,7 +289,7 @@ class Batch:
     def tuning(self):
         """(rows, wavefronts per workgroup, XCD remap, columns per lane,
         batch_items, batch_order, longest captured graph, time steps per
-        launch: 2 if some member takes two-step launches, rows the two-step
+        launch: 2 or 3 if some member takes several, rows those launches'
         loads run ahead)."""
         return capi.trt_batch_get_tuning(self.handle)
 
