@@ -125,7 +125,8 @@ typedef struct {
  * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1600^2 nodes.
  * trt_get_tuning then reports that pass's rows, wavefronts, steps and
  * prefetch (cols_per_lane stays the one-step sweeps').  Setting any of these
- * fields asks for the passes they describe.  Of those lattices, the ones of at
+ * fields asks for the passes they describe; all of them set to what
+ * trt_get_tuning reports keep this one.  Of those lattices, the ones of at
  * most 1024 nodes advance all the steps of a call in one launch, in one
  * workgroup and in place (the reported shape is then unused).  Every choice
  * gives the same bits. */

@@ -397,6 +397,14 @@ bool resident_size(const InstDesc &d) {
     return (int64_t)d.nx * d.ny <= trt::kResidentNodes;
 }
 
+// The launch shape l and the passes that follow from it.
+void set_launch(trt_sim *s, const Launch &l) {
+    s->launch = l;
+    trt::tile(s->desc, l, s->prob.storage);
+    s->narrow = trt::narrow_plan(s->desc, s->prob.storage, l);
+    s->resident = s->narrow.k && resident_size(s->desc);
+}
+
 trt_status check_sim(const trt_sim *s) {
     if (!s) return fail(TRT_EINVAL, "simulation handle is NULL");
     return TRT_OK;
@@ -579,9 +587,7 @@ trt_status trt_create(const trt_problem *p, void *f_a, void *f_b, void *hip_stre
             return fail_hip(e, "mask check");
         }
     }
-    trt::tile(d, s->launch, p->storage);
-    s->narrow = trt::narrow_plan(d, p->storage, s->launch);
-    s->resident = s->narrow.k && resident_size(d);
+    set_launch(s, s->launch);
     // the capture stream is created at the first capture (batch members never
     // capture their own step)
     *out = s;
@@ -594,10 +600,28 @@ trt_status trt_set_tuning(trt_sim *s, const trt_tuning *t) {
     if (st != TRT_OK) return st;
     if (check_sim(s) != TRT_OK) return TRT_EINVAL;
     if (s->in_batch) return fail(TRT_ESTATE, "simulation is a batch member");
-    s->launch = l;
-    trt::tile(s->desc, l, s->prob.storage);
-    s->narrow = trt::narrow_plan(s->desc, s->prob.storage, l);
-    s->resident = s->narrow.k && resident_size(s->desc);
+    set_launch(s, l);
+    // A shape that names, field by field, what the automatic one reports is the
+    // automatic one: trt_get_tuning's answer set again keeps the pass it came
+    // from.  (4096^2 FP64, 14 rows, 4 wavefronts, 3 steps: 0.19 ms per step;
+    // read as a request for the one-step sweep, the only other pass FP64 has,
+    // 0.46.)
+    if (l.rows_per_wave > 0 && l.waves_per_block > 0 && l.steps_per_sweep > 0 &&
+        l.prefetch_rows > 0) {
+        const int cols = s->desc.cols;
+        Launch a = l;
+        a.rows_per_wave = a.waves_per_block = a.cols_per_lane = 0;
+        a.steps_per_sweep = a.prefetch_rows = 0;
+        a.xcd_remap = kDefaultLaunch.xcd_remap;
+        a.remap_asked = 0;
+        set_launch(s, a);
+        const trt::NarrowPlan &p = s->narrow;
+        if (!(p.k == l.steps_per_sweep && p.rows == l.rows_per_wave &&
+              p.waves_per_block == l.waves_per_block && p.depth == l.prefetch_rows &&
+              (!l.remap_asked || p.remap == l.xcd_remap) &&
+              (l.cols_per_lane == 0 || s->desc.cols == cols)))
+            set_launch(s, l);
+    }
     release_graphs(s->graphs);
     return TRT_OK;
 }
