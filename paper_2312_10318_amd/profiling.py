@@ -212,7 +212,7 @@ def summarize(trace_dir, fetch_dir, write_dir, storage, n, steps, warmup, out_pr
     alg = (BYTES_PER_LU[storage] + link_bytes) * nodes * ups
     dur = avg(sweep_ns) * 1e-9
     rec = {
-        "kernel": (re.search(r"(sweep_(single|pair|tb2_batch|tb2|tb3_batch|tb3|batch)|pattern_probe)_kernel(<[^>]*>)?",
+        "kernel": (re.search(r"(sweep_(single|pair|tb2_batch|tb2|tb3_batch|tb3|batch)|narrow_batch|narrow|pattern_probe)_kernel(<[^>]*>)?",
                              kname or "") or re.search(r".*", "sweep")).group(0),
         "workload": wlabel, "storage": storage, "nodes": nodes, "updates_per_launch": ups,
         "source_hash": _run_hash(run_log) if run_log else sweep_source_hash(),
