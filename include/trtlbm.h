@@ -139,7 +139,8 @@ typedef struct {
                                 (on for one simulation -- except three-step launches in
                                 their automatic rows from about 1500^2 nodes on, or of at
                                 least 3072 wavefronts, which run off -- and off for a
-                                batch) */
+                                batch, but for small launches of the one-column
+                                pass) */
     int32_t cols_per_lane;   /* 1 or 2 columns per lane (0: 2 where it applies and nx >= 128) */
     /* Batches only (ignored for one simulation; rows_per_wave > 0 overrides
      * both): how members are cut into work items of one wavefront each. */

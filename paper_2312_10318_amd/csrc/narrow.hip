@@ -586,7 +586,12 @@ hipError_t launch_narrow_batch_t(const InstDesc *descs, int ndescs, const int4 *
     // one-wavefront workgroups while they spread over the CUs at once
     const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
     const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
-    const int r = l.xcd_remap;
+    // Contiguous work items on one XCD, whose L2 then holds the rows and columns
+    // that neighbouring items share, while a launch is small (us per step, the
+    // hardware's order / bands: 24 members of 1.4 M nodes FP32 14.4 / 11.3, FP16
+    // 13.4 / 11.5, FP64 20.9 / 17.5, 16 of 128^2 8.5 / 6.5; 16 of 4.3 M FP64
+    // 53.7 / 54.1; 200 of 13 M FP64 166 / 167).
+    const int r = l.remap_asked ? l.xcd_remap : nitems <= (ST == ST_F64 ? 4096 : 16384);
     const auto launch = [&](auto kernel) {
         kernel<<<g, t, 0, s>>>(descs, ndescs, items, nitems, flip, r);
         return hipGetLastError();
