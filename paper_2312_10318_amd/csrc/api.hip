@@ -213,6 +213,7 @@ struct trt_batch {
     bool buf;  // every member fits one buffer resource
     hipStream_t stream;
     Launch launch;
+    bool built;  // the tables are those of the current members
     InstDesc *d_descs;  // device tables, grown by doubling and reused
     int4 *d_items;
     size_t cap_descs, cap_items;
@@ -1207,6 +1208,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
 }
 
 static trt_status batch_build(trt_batch *b) {
+    b->built = false;
     std::vector<InstDesc> descs;
     std::vector<int4> list;
     batch_tile(b, descs, list);
@@ -1235,6 +1237,7 @@ static trt_status batch_build(trt_batch *b) {
     b->parity2 = 0;
     b->steps = 0;
     release_graphs(b->graphs);
+    b->built = true;
     return TRT_OK;
 }
 
@@ -1456,6 +1459,7 @@ trt_status trt_batch_step(trt_batch *b, int64_t nsteps) {
     if (nsteps < 0) return fail(TRT_EINVAL, "nsteps must be >= 0");
     int64_t n = nsteps;
     if (n == 0) return TRT_OK;
+    if (!b->built) return fail(TRT_ESTATE, "the batch's last rebuild failed");
     if (b->nresident > 0) {
         // independent of the other members: all the call's steps at once
         const int4 *members = b->d_items + b->nitems + b->nitems2 + b->nnarrow[0] + b->nnarrow[1];
@@ -1497,6 +1501,14 @@ trt_status trt_batch_diagnostics(trt_batch *b, double *out) {
     if (!b) return fail(TRT_EINVAL, "batch handle is NULL");
     if (!out) return fail(TRT_EINVAL, "out is NULL");
     const size_t n = b->sims.size();
+    if (!b->built) {
+        // no tables of these members: each from its own descriptor
+        for (size_t k = 0; k < n; ++k) {
+            trt_status st = trt_diagnostics(b->sims[k], out + k * TRT_NDIAG);
+            if (st != TRT_OK) return st;
+        }
+        return TRT_OK;
+    }
     int64_t most = 0;
     for (const trt_sim *s : b->sims) most = std::max(most, (int64_t)s->desc.nx * s->desc.ny);
     TRT_HIP(trt::launch_diagnostics_batch(b->d_descs, (int)n, most, b->storage, b->parity,
