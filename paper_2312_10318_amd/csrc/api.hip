@@ -1501,8 +1501,15 @@ trt_status trt_batch_diagnostics(trt_batch *b, double *out) {
     if (!b) return fail(TRT_EINVAL, "batch handle is NULL");
     if (!out) return fail(TRT_EINVAL, "out is NULL");
     const size_t n = b->sims.size();
-    if (!b->built) {
-        // no tables of these members: each from its own descriptor
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(b->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;
+    }
+    if (!b->built || cap != hipStreamCaptureStatusNone) {
+        // each member from its own descriptor: there are no tables of these
+        // members, or the launches are recorded into a caller's graph, which may
+        // run when the tables hold other members or are gone
         for (size_t k = 0; k < n; ++k) {
             trt_status st = trt_diagnostics(b->sims[k], out + k * TRT_NDIAG);
             if (st != TRT_OK) return st;
