@@ -1043,7 +1043,7 @@ static void batch_narrow_items(trt_batch *b, const std::vector<size_t> &mem, int
         int64_t w = 0;
         for (size_t k : mem) w += trt::narrow_waves(descs[k], b->k2, r);
         return w;
-    });
+    }).rows;
     for (int l = 0; l < 2; ++l) {
         const size_t from = items.size();
         for (size_t k : mem) {
@@ -1111,15 +1111,22 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // 34.4, 5982 36.8 / 39.3; FP16 93 9.9 / 4.3, 1163 15.2 / 11.8, 3373 26.5 /
     // 23.2, 4826 31.3 / 31.9); in FP32 also of twice that many where narrow
     // windows cover the members with a twentieth fewer lanes (5733 windows over
-    // 240 members of 64^2 to 200^2, 8% fewer: 38.8 / 32.0).
+    // 240 members of 64^2 to 200^2, 8% fewer: 38.8 / 32.0).  FP16 below: by the
+    // rounds of both (wide_rounds_f16).
     const int sps = b->launch.steps_per_sweep;
     const bool automatic = sps == 0 && b->launch.rows_per_wave == 0;
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
     int64_t wide_waves = 0, wide_lanes = 0, narrow_lanes = 0, nodes = 0;
+    bool even = true, walls = false;  // all others than resident ones wide, of even width; some with walls
     for (const InstDesc &d : descs) {
-        if (trt::tb2_eligible(d, b->storage) && !resident_size(d)) {
+        const bool wide = trt::tb2_eligible(d, b->storage);
+        if (!resident_size(d)) {
+            even = even && wide && d.nx % 2 == 0;
+            walls = walls || d.links != nullptr;
+        }
+        if (wide && !resident_size(d)) {
             const int valid = trt::narrow_valid(b->k2);
-            wide_waves += (int64_t)((d.nx + trt::kTb2Valid - 1) / trt::kTb2Valid) * ((d.ny + 7) / 8);
+            wide_waves += trt::wide_waves(d, 8);
             wide_lanes += (int64_t)(d.nx + trt::kTb3Valid - 1) / trt::kTb3Valid * 128 * d.ny;
             narrow_lanes += (int64_t)(d.nx + valid - 1) / valid * 64 * d.ny;
         }
@@ -1127,8 +1134,18 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     }
     // FP64: as one lattice of all the members' nodes would (narrow_plan)
     if (automatic && b->storage == trt::ST_F64 && nodes > trt::kThreeStepNodesF64) b->k2 = 3;
-    const bool small = wide_waves < 4096 || (b->storage == trt::ST_F32 && wide_waves < 8192 &&
-                                             20 * narrow_lanes < 19 * wide_lanes);
+    bool small = wide_waves < 4096 || (b->storage == trt::ST_F32 && wide_waves < 8192 &&
+                                       20 * narrow_lanes < 19 * wide_lanes);
+    if (small && b->storage == trt::ST_F16 && even) {
+        const auto waves = [&](int r) {
+            int64_t w = 0;
+            for (const InstDesc &d : descs)
+                if (!resident_size(d)) w += trt::narrow_waves(d, b->k2, r);
+            return w;
+        };
+        small = !trt::wide_rounds_f16(
+            wide_waves, trt::narrow_rows(b->storage, b->k2, walls, nodes, waves).cost, walls);
+    }
     b->cls.assign(n, kOneStep);
     b->multi = false;
     for (size_t k = 0; k < n; ++k) {

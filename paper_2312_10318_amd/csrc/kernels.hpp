@@ -184,6 +184,10 @@ InstDesc narrow_desc(const InstDesc &d, int k, int rows);
 inline int64_t narrow_waves(const InstDesc &d, int k, int r) {
     return (int64_t)((d.nx + narrow_valid(k) - 1) / narrow_valid(k)) * ((d.ny + r - 1) / r);
 }
+// Wavefronts of 128-column windows of two steps in blocks of r rows.
+inline int64_t wide_waves(const InstDesc &d, int r) {
+    return (int64_t)((d.nx + kTb2Valid - 1) / kTb2Valid) * ((d.ny + r - 1) / r);
+}
 // Rows ahead of their use that a launch of `waves` wavefronts loads: two where
 // a wavefront is alone on its SIMD or nearly so, and FP16 always (see
 // narrow_plan); one for FP64's three steps.
@@ -191,9 +195,14 @@ inline int narrow_depth(int storage, int k, int64_t waves) {
     if (storage == ST_F64 && k == 3) return 1;
     return storage == ST_F16 || waves <= 2048 ? 2 : 1;
 }
-// Rows per block, from waves(r), the wavefronts that blocks of r rows give (the
-// reasons and figures: narrow_plan).
-template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes, W waves) {
+// Rows per block, from waves(r), the wavefronts that blocks of r rows give, and
+// their cost where it is by rounds (the reasons and figures: narrow_plan).
+struct NarrowRows {
+    int rows;
+    int64_t cost;
+};
+template <class W>
+NarrowRows narrow_rows(int storage, int k, bool links, int64_t nodes, W waves) {
     const bool far = nodes > 5 * 1024 * 1024 / 2;  // FP64 beyond the memory-side cache
     if (storage == ST_F64 ? k == 2 || far : storage == ST_F32 && k == 2) {
         int cap = 8;
@@ -203,7 +212,7 @@ template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes
         // (FP32 with a link map: two)
         int r = waves(1) <= (storage == ST_F32 && links ? 2048 : 1024) ? 1 : 2;
         while (r < cap && waves(r) > most) ++r;
-        return r;
+        return {r, 0};
     }
     // the cheapest: a block's rows and `fill` more, times the rounds of `each`
     // wavefronts per SIMD, where a round of m costs start + 2 m
@@ -223,7 +232,24 @@ template <class W> int narrow_rows(int storage, int k, bool links, int64_t nodes
             least = c;
         }
     }
-    return best;
+    return {best, least};
+}
+// FP16 lattices of even width without a link map or with whole-row walls: whether
+// the two-step launches of `wide` 128-column wavefronts in blocks of 8 rows, at
+// most 4096, are the faster ones where the 64-column rows cost `cost`.  Both go by
+// rounds of 1024 wavefronts, and their rounds fill at different sizes.  us per
+// step, 64 columns / 128: 1250^2 11.9 / 12.9, 1300^2 14.0 / 12.8, 1450^2 14.6 /
+// 16.3, 1600^2 19.3 / 16.6, 1052 x 1750 14.9 / 13.1, channels 1450^2 15.3 / 17.7,
+// 1600^2 20.0 / 18.0; 7 lattices of 500^2 13.5 / 16.6, 9 18.1 / 16.8, 10 19.5 /
+// 21.9; 5 of 700^2 19.5 / 16.9, channels 19.9 / 18.2.  The costs from which one,
+// two, three and four rounds win were read off 210 lattices and batches: the
+// faster pass, or within 2% of it, at all but seven of them (5%).  Odd widths cost the
+// 128-column pass 1.5 to 2 us more, and there the 64-column one always won (1563 x
+// 1311 16.7 / 18.1; 36 lattices of 64 to 600 columns 23.5 / 29.5).
+inline bool wide_rounds_f16(int64_t wide, int64_t cost, bool links) {
+    constexpr int from[2][4] = {{49, 73, 98, 136}, {133, 201, 269, 337}};
+    const int64_t n = (wide + 1023) / 1024;
+    return n > 0 && cost >= from[links][n < 4 ? n - 1 : 3];
 }
 // k steps of the batch members named by items, as launch_sweep_tb2_batch
 // (descs tiled by narrow_desc; the members with a link map and those without

@@ -675,7 +675,9 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     19.6, 2048^2 27.3 against 27.9.  1024^2 alone keeps two steps and eight
 //     rows (10.6; 8.2 with three; 12.6 before): callers rely on that default.
 //   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
-//     14.9, 2048^2 25.9 / 27.3 (so not there); cylinder 1050^2 21.1 / 11.0;
+//     14.9, 2048^2 25.9 / 27.3 (so not there, and of even width below that only
+//     where the 128-column launches leave their last round idle:
+//     wide_rounds_f16); cylinder 1050^2 21.1 / 11.0;
 //     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
 // Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows.  FP64, and two
 // steps in FP32: the smallest R that leaves at most two wavefronts per SIMD
@@ -720,7 +722,11 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
         return p0;
     }
     const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };
-    p.rows = narrow_rows(storage, p.k, d.links != nullptr, nodes, waves);
+    const NarrowRows r = narrow_rows(storage, p.k, d.links != nullptr, nodes, waves);
+    if (storage == ST_F16 && wide && d.nx % 2 == 0 &&
+        wide_rounds_f16(wide_waves(d, 8), r.cost, d.links != nullptr))
+        return p0;
+    p.rows = r.rows;
     p.depth = narrow_depth(storage, p.k, waves(p.rows));
     p.waves_per_block = waves(p.rows) >= 4096 ? 4 : 1;
     // XCD bands, but for the large launches of FP64's three steps (2048^2 at 14
