@@ -241,13 +241,15 @@ struct trt_batch {
     // that take several steps per launch, tiled for their pass, follow the n
     // one-step ones; their items follow the one-step items: those of the
     // 128-column windows, then those of the 64-column windows without and with
-    // a link map; then one entry per resident member.
+    // a link map; then one entry per resident member; then one MemberDiag per
+    // member (at diag_at).
     std::vector<char> cls;
     int nitems0;    // one-step items of class-0 members (a prefix of the list)
     int nitems2;    // items of 128-column windows
     int nnarrow[2]; // items of 64-column windows without, with a link map
     int nresident, resident_nodes;  // resident members, the largest one's nodes
     int ndescs2;    // descriptors tiled for launches of several steps
+    size_t diag_at;
     bool deep2;     // two-step launches load two rows ahead
     bool multi;     // some member takes several steps per launch
     int k2;         // how many: 2 or 3
@@ -512,8 +514,6 @@ void fill_desc(InstDesc &d, const trt_problem *p, void *f_a, void *f_b) {
     d.gy = p->gy;
     d.xbc = p->x_boundary == TRT_X_INFLOW_OUTFLOW ? 1 : 0;
     d.cls = 0;
-    d.time0 = 0;
-    d.partials = nullptr;
     d.u_in = d.xbc ? p->u_in : 0.0;
     d.rho_in = d.xbc ? p->rho_in : 1.0;
     d.rho_out = d.xbc ? p->rho_out : 1.0;
@@ -563,7 +563,6 @@ trt_status trt_create(const trt_problem *p, void *f_a, void *f_b, void *hip_stre
         delete s;
         return fail_hip(e, "hipMalloc(scratch)");
     }
-    d.partials = s->scratch;
     if (needs_links(p)) {
         e = hipMalloc((void **)&s->links, link_alloc_bytes(p->nx, p->ny));
         if (e == hipSuccess) {
@@ -1077,7 +1076,6 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
         InstDesc &d = descs[k];
         d = b->sims[k]->desc;
         d.cur = b->sims[k]->cur;
-        d.time0 = b->sims[k]->time;
         trt::tile(d, b->launch, b->sims[k]->prob.storage);
     }
     if (b->launch.rows_per_wave <= 0 && b->launch.batch_items > 0) {
@@ -1222,6 +1220,14 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
             ++b->nresident;
             b->resident_nodes = std::max(b->resident_nodes, descs[k].nx * descs[k].ny);
         }
+    b->diag_at = items.size();
+    for (const trt_sim *s : b->sims) {
+        const trt::MemberDiag m = {s->scratch, s->time};
+        int4 word;
+        static_assert(sizeof(m) == sizeof(word), "one entry of the list");
+        memcpy(&word, &m, sizeof(word));
+        items.push_back(word);
+    }
 }
 
 static trt_status batch_build(trt_batch *b) {
@@ -1535,9 +1541,9 @@ trt_status trt_batch_diagnostics(trt_batch *b, double *out) {
     }
     int64_t most = 0;
     for (const trt_sim *s : b->sims) most = std::max(most, (int64_t)s->desc.nx * s->desc.ny);
-    TRT_HIP(trt::launch_diagnostics_batch(b->d_descs, (int)n, most, b->storage, b->parity,
-                                          b->multi ? b->parity2 : b->parity, b->steps, out,
-                                          b->stream));
+    TRT_HIP(trt::launch_diagnostics_batch(
+        b->d_descs, reinterpret_cast<const trt::MemberDiag *>(b->d_items + b->diag_at), (int)n, most,
+        b->storage, b->parity, b->multi ? b->parity2 : b->parity, b->steps, out, b->stream));
     return TRT_OK;
 }
 

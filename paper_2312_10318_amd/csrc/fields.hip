@@ -301,20 +301,22 @@ __global__ __launch_bounds__(kDiagThreads) void diag_final_kernel(
 // sum: 31% of a 60-step pass of 48 members.
 template <int ST>
 __global__ __launch_bounds__(kDiagThreads) void diag_batch_kernel(
-    const InstDesc *__restrict__ descs, int first, int flip0, int flip1) {
+    const InstDesc *__restrict__ descs, const MemberDiag *__restrict__ members, int first,
+    int flip0, int flip1) {
     const InstDesc d = descs[first + blockIdx.y];
     const int blocks = diag_blocks((int64_t)d.nx * d.ny);
     if ((int)blockIdx.x >= blocks) return;
     const int flip = d.cls == 0 ? flip0 : (d.cls == 1 ? flip1 : 0);
-    diag_block<ST>(d, d.cur ^ flip, blockIdx.x, blocks, d.partials);
+    diag_block<ST>(d, d.cur ^ flip, blockIdx.x, blocks, members[first + blockIdx.y].partials);
 }
 
 __global__ __launch_bounds__(kDiagThreads) void diag_batch_final_kernel(
-    const InstDesc *__restrict__ descs, int first, double *__restrict__ out, int64_t steps) {
+    const InstDesc *__restrict__ descs, const MemberDiag *__restrict__ members, int first,
+    double *__restrict__ out, int64_t steps) {
     const int k = first + blockIdx.x;
-    const InstDesc d = descs[k];
-    diag_final(d.partials, diag_blocks((int64_t)d.nx * d.ny), out + (int64_t)k * TRT_NDIAG,
-               (double)(d.time0 + steps));
+    const MemberDiag m = members[k];
+    diag_final(m.partials, diag_blocks((int64_t)descs[k].nx * descs[k].ny),
+               out + (int64_t)k * TRT_NDIAG, (double)(m.time0 + steps));
 }
 
 template <int ST>
@@ -562,18 +564,18 @@ hipError_t launch_diagnostics(const InstDesc &d, int storage, int src, double *p
     return hipGetLastError();
 }
 
-hipError_t launch_diagnostics_batch(const InstDesc *descs, int n, int64_t most_nodes, int storage,
-                                    int flip0, int flip1, int64_t steps, double *out,
-                                    hipStream_t stream) {
+hipError_t launch_diagnostics_batch(const InstDesc *descs, const MemberDiag *members, int n,
+                                    int64_t most_nodes, int storage, int flip0, int flip1,
+                                    int64_t steps, double *out, hipStream_t stream) {
     const int blocks = diag_blocks(most_nodes);
     constexpr int kMembers = 32768;  // per launch: the grid's y extent
     for (int first = 0; first < n; first += kMembers) {
         const int m = n - first < kMembers ? n - first : kMembers;
         TRT_DISPATCH(storage, (diag_batch_kernel<S><<<dim3(blocks, m), kDiagThreads, 0, stream>>>(
-                                  descs, first, flip0, flip1)));
+                                  descs, members, first, flip0, flip1)));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        diag_batch_final_kernel<<<m, kDiagThreads, 0, stream>>>(descs, first, out, steps);
+        diag_batch_final_kernel<<<m, kDiagThreads, 0, stream>>>(descs, members, first, out, steps);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

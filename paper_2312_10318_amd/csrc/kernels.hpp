@@ -301,12 +301,12 @@ hipError_t launch_macros(const InstDesc &d, int storage, int src, double *rho, d
 int diag_partial_count();
 hipError_t launch_diagnostics(const InstDesc &d, int storage, int src, double *partials,
                               double *out, double time, hipStream_t stream);
-// Diagnostics of the n members of a batch (descs: its device table): member
-// k, which reads buf[cur ^ flip0] (cls 0), buf[cur ^ flip1] (1) or buf[cur] and is `steps` steps past
+// Diagnostics of the n members of a batch (descs, members: its device tables):
+// member k, which reads buf[cur ^ flip0] (cls 0), buf[cur ^ flip1] (1) or buf[cur] and is `steps` steps past
 // its time0, writes out[k][TRT_NDIAG].  most_nodes: the largest member's.
-hipError_t launch_diagnostics_batch(const InstDesc *descs, int n, int64_t most_nodes, int storage,
-                                    int flip0, int flip1, int64_t steps, double *out,
-                                    hipStream_t stream);
+hipError_t launch_diagnostics_batch(const InstDesc *descs, const MemberDiag *members, int n,
+                                    int64_t most_nodes, int storage, int flip0, int flip1,
+                                    int64_t steps, double *out, hipStream_t stream);
 hipError_t launch_row_mean_ux(const InstDesc &d, int storage, int src, double *out,
                               hipStream_t stream);
 
