@@ -214,17 +214,20 @@ struct trt_batch {
     hipStream_t stream;
     Launch launch;
     bool built;  // the tables are those of the current members
-    InstDesc *d_descs;  // device tables, grown by doubling and reused
+    // Device tables, the descriptors and the work list behind them, in one
+    // allocation that one copy fills (16 FP64 lattices of 128^2, us per
+    // membership change: two copies 24.6, one 16.2).
+    char *d_table;
+    size_t cap_table;
+    InstDesc *d_descs;
     int4 *d_items;
-    size_t cap_descs, cap_items;
     // Pinned staging of the tables: a ring of slots, each reused only once
     // the copy that last read it has run (its event), so a membership
     // change waits for a copy several changes old, not for the work queued
     // on the stream ahead of the latest one.
     struct Staging {
-        InstDesc *descs;
-        int4 *items;
-        size_t cap_descs, cap_items;
+        char *table;
+        size_t cap;
         hipEvent_t done;
         bool pending;
     };
@@ -944,35 +947,33 @@ void trt_destroy(trt_sim *s) {
 
 // ---------------------------------------------------------------- batches
 
-// Grow a device or pinned host buffer to at least `need` elements (contents
-// are not kept).
+// Grow a device or pinned host buffer to at least `need` bytes (contents are not
+// kept).
 extern "C++" {
-// Table capacity for `need` entries: at least 4096, growing fourfold, so a
+// Table capacity for `need` bytes: at least 256 KiB, growing fourfold, so a
 // batch whose membership keeps changing reallocates rarely.
 static size_t table_capacity(size_t cap, size_t need) {
-    size_t c = cap ? cap : 4096;
+    size_t c = cap ? cap : 256 * 1024;
     while (c < need) c *= 4;
     return c;
 }
-template <class E>
-static hipError_t grow_device(E *&p, size_t &cap, size_t need, std::vector<void *> &retired) {
+static hipError_t grow_device(char *&p, size_t &cap, size_t need, std::vector<void *> &retired) {
     if (need <= cap && p) return hipSuccess;
     const size_t c = table_capacity(cap, need);
     if (p) retired.push_back(p);
     p = nullptr;
     cap = 0;
-    hipError_t e = hipMalloc((void **)&p, c * sizeof(E));
+    hipError_t e = hipMalloc((void **)&p, c);
     if (e == hipSuccess) cap = c;
     return e;
 }
-template <class E>
-static hipError_t grow_pinned(E *&p, size_t &cap, size_t need, std::vector<void *> &retired) {
+static hipError_t grow_pinned(char *&p, size_t &cap, size_t need, std::vector<void *> &retired) {
     if (need <= cap && p) return hipSuccess;
     const size_t c = table_capacity(cap, need);
     if (p) retired.push_back(p);
     p = nullptr;
     cap = 0;
-    hipError_t e = hipHostMalloc((void **)&p, c * sizeof(E), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)&p, c, hipHostMallocDefault);
     if (e == hipSuccess) cap = c;
     return e;
 }
@@ -1235,7 +1236,6 @@ static trt_status batch_build(trt_batch *b) {
     std::vector<InstDesc> descs;
     std::vector<int4> list;
     batch_tile(b, descs, list);
-    const size_t n = descs.size();
     const size_t nitems = list.size();
     if (nitems > (size_t)INT32_MAX) return fail(TRT_EINVAL, "batch work list too long");
     trt_batch::Staging &sg = b->stage[b->next_stage];
@@ -1244,16 +1244,15 @@ static trt_status batch_build(trt_batch *b) {
         TRT_HIP(hipEventSynchronize(sg.done));
         sg.pending = false;
     }
-    TRT_HIP(grow_pinned(sg.descs, sg.cap_descs, n, b->retired_host));
-    TRT_HIP(grow_pinned(sg.items, sg.cap_items, nitems, b->retired_host));
-    TRT_HIP(grow_device(b->d_descs, b->cap_descs, n, b->retired_dev));
-    TRT_HIP(grow_device(b->d_items, b->cap_items, nitems, b->retired_dev));
-    for (size_t k = 0; k < n; ++k) sg.descs[k] = descs[k];
-    for (size_t j = 0; j < nitems; ++j) sg.items[j] = list[j];
-    TRT_HIP(hipMemcpyAsync(b->d_descs, sg.descs, n * sizeof(InstDesc), hipMemcpyHostToDevice,
-                           b->stream));
-    TRT_HIP(hipMemcpyAsync(b->d_items, sg.items, nitems * sizeof(int4), hipMemcpyHostToDevice,
-                           b->stream));
+    const size_t desc_bytes = descs.size() * sizeof(InstDesc);
+    const size_t at = (desc_bytes + 255) / 256 * 256, bytes = at + nitems * sizeof(int4);
+    TRT_HIP(grow_pinned(sg.table, sg.cap, bytes, b->retired_host));
+    TRT_HIP(grow_device(b->d_table, b->cap_table, bytes, b->retired_dev));
+    b->d_descs = reinterpret_cast<InstDesc *>(b->d_table);
+    b->d_items = reinterpret_cast<int4 *>(b->d_table + at);
+    memcpy(sg.table, descs.data(), desc_bytes);
+    memcpy(sg.table + at, list.data(), nitems * sizeof(int4));
+    TRT_HIP(hipMemcpyAsync(b->d_table, sg.table, bytes, hipMemcpyHostToDevice, b->stream));
     TRT_HIP(hipEventRecord(sg.done, b->stream));
     sg.pending = true;
     b->parity = 0;
@@ -1554,12 +1553,10 @@ void trt_batch_destroy(trt_batch *b) {
     for (auto &sg : b->stage) {
         if (sg.pending) (void)hipEventSynchronize(sg.done);
         if (sg.done) (void)hipEventDestroy(sg.done);
-        if (sg.descs) (void)hipHostFree(sg.descs);
-        if (sg.items) (void)hipHostFree(sg.items);
+        if (sg.table) (void)hipHostFree(sg.table);
     }
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
-    if (b->d_descs) (void)hipFree(b->d_descs);
-    if (b->d_items) (void)hipFree(b->d_items);
+    if (b->d_table) (void)hipFree(b->d_table);
     for (void *p : b->retired_dev) (void)hipFree(p);
     for (void *p : b->retired_host) (void)hipHostFree(p);
     delete b;

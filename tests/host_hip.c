@@ -14,10 +14,11 @@ static struct { const void *host; const char *name; } kernels[kMaxKernels];
 static int nkernels;
 static struct { const char *name; uint32_t gx, gy; uint64_t word; int32_t second; } log_[kMaxLaunches];
 static int nlog;
-static int fail_device, fail_pinned, capturing;
+static int fail_device, fail_pinned, capturing, ncopies;
 
 /* the tests' side */
-void host_clear(void) { nlog = 0; }
+void host_clear(void) { nlog = ncopies = 0; }
+int host_copies(void) { return ncopies; }
 int host_launches(void) { return nlog; }
 const char *host_kernel(int i) { return log_[i].name; }
 uint64_t host_word(int i) { return log_[i].word; }
@@ -77,6 +78,7 @@ int hipHostMalloc(void **p, size_t n, unsigned f) {
 int hipHostFree(void *p) { free(p); return 0; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) {
     (void)k; (void)st;
+    ++ncopies;
     memcpy(d, s, n);
     return 0;
 }
