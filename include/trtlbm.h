@@ -375,7 +375,8 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims);
  * an automatic launch shape every member of at least 16 rows within 4 GiB
  * advances two or three steps per launch (FP32 three, FP16 two, FP64 three
  * in batches of more than about 3.9e5 nodes, else two), members of at most
- * 1024 nodes all the steps of the call in one launch; steps_per_sweep or
+ * 1024 nodes all the steps of the call in one launch (a few of them beside
+ * larger members: as those); steps_per_sweep or
  * rows_per_wave set, those that the passes of trt_tuning allow, and the others
  * by one-step sweeps in the same graphs.  Every member gets the bits it gets
  * alone. */

@@ -1145,6 +1145,28 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
         small = !trt::wide_rounds_f16(
             wide_waves, trt::narrow_rows(b->storage, b->k2, walls, nodes, waves).cost, walls);
     }
+    // Members of at most kResidentNodes nodes are resident, but a few of them ride
+    // in the launches of others that take several steps: the resident launch, a
+    // workgroup a member, would run ahead of those and add its 0.8 to 1.3 us to
+    // every step.  us per step, one-step sweeps or 128 columns before / resident /
+    // riding: one 32^2 beside four of 1024^2 FP16 25.6 / 26.7 / 25.8, FP32 32.3 /
+    // 28.5 / 27.8; 8 beside four of 128^2 FP64 8.6 / 4.5 / 3.4.  Many cost more as
+    // windows than they add as workgroups (256 beside 64^2 FP64 3.8 / 8.2, 32 beside
+    // 64 lattices of 64 to 600 FP32 39.4 / 42.0), and so does one that opens
+    // another round of wavefronts in FP16's 128-column launches (beside sixteen of
+    // 512^2 27.2 / 29.3).
+    int64_t tiny = 0, tiny_waves = 0, others = 0;
+    for (const InstDesc &d : descs) {
+        if (resident_size(d)) {
+            ++tiny;
+            if (trt::tb2_eligible(d, b->storage)) tiny_waves += trt::wide_waves(d, 8);
+        } else if (trt::narrow_eligible(d, b->storage) || trt::tb2_eligible(d, b->storage)) {
+            ++others;
+        }
+    }
+    const auto rounds = [](int64_t w) { return (w + 1023) / 1024; };
+    const bool ride = others > 0 && tiny <= (b->storage == trt::ST_F16 && !small ? 32 : 16) &&
+                      (small || b->k2 == 3 || rounds(wide_waves + tiny_waves) == rounds(wide_waves));
     b->cls.assign(n, kOneStep);
     b->multi = false;
     for (size_t k = 0; k < n; ++k) {
@@ -1152,7 +1174,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
         const bool wide = sps != 1 && (b->k2 == 3 ? trt::tb3_eligible(d, b->storage)
                                                   : trt::tb2_eligible(d, b->storage));
         const bool narrow = automatic && trt::narrow_eligible(d, b->storage);
-        if (narrow && resident_size(d))
+        if (narrow && resident_size(d) && !ride)
             b->cls[k] = kResident;
         else if (narrow && (!wide || small))
             b->cls[k] = kNarrow;
