@@ -253,7 +253,8 @@ struct trt_batch {
     int nresident, resident_nodes;  // resident members, the largest one's nodes
     int ndescs2;    // descriptors tiled for launches of several steps
     size_t diag_at;
-    bool deep2;     // two-step launches load two rows ahead
+    bool deep2;     // two-step launches of 128-column windows load two rows ahead
+    bool deep;      // and launches of either kind of windows do
     bool multi;     // some member takes several steps per launch
     int k2;         // how many: 2 or 3
     int64_t steps;  // time steps since the tables were built
@@ -1056,6 +1057,8 @@ static void batch_narrow_items(trt_batch *b, const std::vector<size_t> &mem, int
         }
         order(from);
         b->nnarrow[l] = (int)(items.size() - from);
+        b->deep = b->deep ||
+                  (b->nnarrow[l] > 0 && trt::narrow_depth(b->storage, b->k2, b->nnarrow[l]) == 2);
     }
 }
 
@@ -1233,8 +1236,10 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     }
     b->nitems2 = b->nnarrow[0] = b->nnarrow[1] = 0;
     b->deep2 = false;
+    b->deep = false;
     if (!mem.empty()) batch_wide_items(b, mem, descs, items, order);
     if (!narrow.empty()) batch_narrow_items(b, narrow, nodes, n, descs, items, order);
+    b->deep = b->deep || b->deep2;
     b->ndescs2 = (int)(descs.size() - n);
     b->nresident = b->resident_nodes = 0;
     for (size_t k = 0; k < n; ++k)
@@ -1380,7 +1385,7 @@ trt_status trt_batch_get_tuning(const trt_batch *b, trt_tuning *t) {
     t->batch_order = b->launch.batch_order;
     t->graph_steps = b->launch.graph_steps;
     t->steps_per_sweep = b->multi ? b->k2 : 1;
-    t->prefetch_rows = b->multi ? (b->deep2 ? 2 : 1) : 0;
+    t->prefetch_rows = b->multi ? (b->deep ? 2 : 1) : 0;
     return TRT_OK;
 }
 

@@ -1,0 +1,39 @@
+"""The launch shape that a batch reports."""
+import host_hip
+
+BATCHES = {
+    "f64 two steps": ("f64", [(130, 100), (64, 33)], 0),
+    "f64 three steps": ("f64", [(700, 800)], 0),
+    "f64 open boundaries": ("f64", [(130, 100), (90, 70)], 2),
+    "f64 one step": ("f64", [(130, 12)], 0),
+    "f32 64 columns": ("f32", [(200, 100)] * 3, 1),
+    "f32 64 columns, many": ("f32", [(500, 400)] * 9, 0),
+    "f32 128 columns": ("f32", [(1500, 1500)] * 4, 0),
+    "f16 64 columns": ("f16", [(130, 100)] * 4, 1),
+    "f16 128 columns": ("f16", [(1500, 1500)] * 4, 0),
+    "f16 both": ("f16", [(130, 100)] + [(1500, 1500)] * 4, 1),
+    "resident": ("f64", [(32, 32), (4, 34)], 0),
+    "resident and others": ("f32", [(32, 32)] * 40 + [(300, 300)], 0),
+}
+# rows ahead that its launches of several steps load
+PREFETCH = {
+    "f64 two steps": 2, "f64 three steps": 1, "f64 open boundaries": 2, "f64 one step": 0,
+    "f32 64 columns": 2, "f32 64 columns, many": 1, "f32 128 columns": 1, "f16 64 columns": 2,
+    "f16 128 columns": 1, "f16 both": 2, "resident": 0, "resident and others": 2,
+}
+
+
+def _batch(name):
+    """The batch; its first `inflows` members have open boundaries."""
+    storage, sizes, inflows = BATCHES[name]
+    return host_hip.capi.trt_batch_create([host_hip.sim(nx, ny, storage, inflow=k < inflows)[0]
+                                           for k, (nx, ny) in enumerate(sizes)])
+
+
+def prefetch():
+    for name, want in PREFETCH.items():
+        assert host_hip.capi.trt_batch_get_tuning(_batch(name))[8] == want, name
+
+
+def test_prefetch_of_every_kind_of_launch(tmp_path):
+    host_hip.in_process("test_batch_tuning_cpu", "prefetch", str(tmp_path))
