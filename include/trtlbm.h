@@ -376,10 +376,11 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims);
  * advances two or three steps per launch (FP32 three, FP16 two, FP64 three
  * in batches of more than about 3.9e5 nodes, else two), members of at most
  * 1024 nodes all the steps of the call in one launch (a few of them beside
- * larger members: as those); steps_per_sweep or
- * rows_per_wave set, those that the passes of trt_tuning allow, and the others
- * by one-step sweeps in the same graphs.  Every member gets the bits it gets
- * alone. */
+ * larger members: as those); with a field set that describes
+ * a pass (rows_per_wave, waves_per_block, cols_per_lane, steps_per_sweep,
+ * prefetch_rows or batch_items > 0), those that the 128-column passes of
+ * trt_tuning allow, and the others by one-step sweeps in the same graphs.  Every
+ * member gets the bits it gets alone. */
 trt_status trt_batch_step(trt_batch *b, int64_t nsteps);
 
 /* Diagnostics of every member into device out[n][TRT_NDIAG]. */

@@ -1103,7 +1103,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // (unless two are asked for), two in FP16.  The 256-member benchmark batch
     // (sides 64 to 1024), FP32: 155.4 GLUPS with three steps per launch against
     // 118.0 with two -- its members are small, but together they far exceed
-    // the memory-side cache.  With rows and steps automatic: members of at most
+    // the memory-side cache.  With no field set that describes a pass: members of at most
     // kResidentNodes nodes are resident; those the 128-column passes do not
     // take (FP64, link maps other than whole-row walls) are narrow, two steps
     // per launch (FP32: as the wide members); and so are all members of a
@@ -1116,7 +1116,7 @@ static void batch_tile(trt_batch *b, std::vector<InstDesc> &descs, std::vector<i
     // 240 members of 64^2 to 200^2, 8% fewer: 38.8 / 32.0).  FP16 below: by the
     // rounds of both (wide_rounds_f16).
     const int sps = b->launch.steps_per_sweep;
-    const bool automatic = sps == 0 && b->launch.rows_per_wave == 0;
+    const bool automatic = trt::automatic(b->launch) && b->launch.batch_items <= 0;
     b->k2 = ((sps == 0 || sps == 3) && b->storage == trt::ST_F32) ? 3 : 2;
     int64_t wide_waves = 0, wide_lanes = 0, narrow_lanes = 0, nodes = 0;
     bool even = true, walls = false;  // all others than resident ones wide, of even width; some with walls

@@ -25,6 +25,12 @@ struct Launch {
     int remap_asked;      // xcd_remap was set by the caller (else the pass's default)
 };
 
+// Whether the passes are the library's choice: no field is set that describes one.
+inline bool automatic(const Launch &l) {
+    return l.rows_per_wave == 0 && l.waves_per_block == 0 && l.cols_per_lane == 0 &&
+           l.steps_per_sweep == 0 && l.prefetch_rows == 0;
+}
+
 // Wavefronts per workgroup of a single-lattice sweep.  The one-column
 // kernels take at most 4 (256 threads), the two-column kernels 16 (FP64:
 // 8, for its register budget).  The two-column workgroups are synchronised

@@ -584,7 +584,7 @@ template <int ST, int K>
 hipError_t launch_narrow_batch_t(const InstDesc *descs, int ndescs, const int4 *items, int nitems,
                                  bool links, int flip, const Launch &l, hipStream_t s) {
     // one-wavefront workgroups while they spread over the CUs at once
-    const int wpb = l.waves_per_block > 0 || nitems > 4096 ? batch_waves_per_block(l) : 1;
+    const int wpb = nitems > 4096 ? kNarrowMaxWaves : 1;
     const dim3 g((nitems + wpb - 1) / wpb), t(64 * wpb);
     // Contiguous work items on one XCD, whose L2 then holds the rows and columns
     // that neighbouring items share, while a launch is small (us per step, the
@@ -704,9 +704,7 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
     const NarrowPlan p0 = {0, 0, 0, 0, 1};
     NarrowPlan p = p0;
-    const bool automatic = l.rows_per_wave == 0 && l.waves_per_block == 0 && l.cols_per_lane == 0 &&
-                           l.steps_per_sweep == 0 && l.prefetch_rows == 0;
-    if (!automatic || !narrow_eligible(d, storage)) return p;
+    if (!automatic(l) || !narrow_eligible(d, storage)) return p;
     const int64_t nodes = (int64_t)d.nx * d.ny;
     const bool wide = tb2_eligible(d, storage);  // the 128-column passes apply
     constexpr int64_t k1 = 1024;

@@ -1,4 +1,4 @@
-"""The launch shape that a batch reports."""
+"""The launch shape that a batch reports, and the launches that a set one asks for."""
 import host_hip
 
 BATCHES = {
@@ -37,3 +37,35 @@ def prefetch():
 
 def test_prefetch_of_every_kind_of_launch(tmp_path):
     host_hip.in_process("test_batch_tuning_cpu", "prefetch", str(tmp_path))
+
+
+def _step(b, n=6):
+    """The launches of n steps in one call, from its first lattices: kernels, grids."""
+    host_hip.clear()
+    host_hip.capi.trt_batch_step(b, n)
+    return [(k, host_hip.hip.host_grid(i, 0)) for i, (k, _, _) in enumerate(host_hip.launches())]
+
+
+def _new_passes(b):
+    return any("narrow" in k or "resident" in k for k, _ in _step(b))
+
+
+def requests():
+    capi = host_hip.capi
+    fields = (dict(rows_per_wave=8), dict(waves_per_block=2), dict(cols_per_lane=1),
+              dict(steps_per_sweep=2), dict(steps_per_sweep=1), dict(prefetch_rows=1),
+              dict(batch_items=16384))
+    others = (dict(xcd_remap=1), dict(batch_order=2), dict(graph_steps=8), dict(batch_items=-1))
+    for name in ("f64 two steps", "f64 three steps", "f64 open boundaries", "f32 64 columns",
+                 "f16 64 columns", "resident", "resident and others"):
+        assert _new_passes(_batch(name)), name
+        for kw in fields + others:
+            b = _batch(name)
+            capi.trt_batch_set_tuning(b, **kw)
+            assert _new_passes(b) == (kw in others), (name, kw)
+            capi.trt_batch_set_tuning(b)
+            assert _new_passes(b), (name, kw)
+
+
+def test_a_set_field_asks_for_the_passes_it_describes(tmp_path):
+    host_hip.in_process("test_batch_tuning_cpu", "requests", str(tmp_path))
