@@ -392,7 +392,7 @@ trt_status trt_batch_set_tuning(trt_batch *b, const trt_tuning *t);
 /* The batch's launch shape as set (0 where automatic); steps_per_sweep
  * reports 2 or 3 only if some member takes launches of several steps,
  * prefetch_rows the rows ahead in effect, the most of any of those launches (0
- * without such members).  EINVAL
+ * without such members).  Set again as reported, it keeps the passes.  EINVAL
  * for a NULL handle or out. */
 trt_status trt_batch_get_tuning(const trt_batch *b, trt_tuning *t);
 

@@ -1361,6 +1361,27 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims) {
     });
 }
 
+// Whether l names, field by field, what the automatic shape reports for the
+// batch's members (the steps and rows ahead may be left open): set again, a
+// reported shape keeps the passes it came from.  (us per
+// step, read as a request for the passes those fields describe / as the automatic
+// shape: ten FP64 lattices of 4 x 34 6.6 / 0.62, 16 of 128^2 13.4 / 5.7.)
+static bool batch_names_automatic(trt_batch *b, const Launch &l) {
+    if (l.rows_per_wave != 0 || l.cols_per_lane != 0 || l.batch_items > 0 || !l.remap_asked ||
+        l.waves_per_block != trt::batch_waves_per_block(kBatchDefaultLaunch))
+        return false;
+    if (l.steps_per_sweep == 0 && l.prefetch_rows == 0) return true;
+    b->built = false;  // the members' classes change; the caller rebuilds
+    b->launch = l;
+    b->launch.waves_per_block = b->launch.steps_per_sweep = b->launch.prefetch_rows = 0;
+    std::vector<InstDesc> descs;
+    std::vector<int4> list;
+    batch_tile(b, descs, list);
+    trt_tuning r;
+    (void)trt_batch_get_tuning(b, &r);
+    return r.steps_per_sweep == l.steps_per_sweep && r.prefetch_rows == l.prefetch_rows;
+}
+
 trt_status trt_batch_set_tuning(trt_batch *b, const trt_tuning *t) {
     Launch l;
     trt_status st = check_launch(t, l, kBatchDefaultLaunch);
@@ -1368,8 +1389,14 @@ trt_status trt_batch_set_tuning(trt_batch *b, const trt_tuning *t) {
     if (!b) return fail(TRT_EINVAL, "batch handle is NULL");
     // members' cur already reflects every step taken; rebuilding restarts
     // the batch parity from there
-    b->launch = l;
-    return guarded([&] { return batch_build(b); });
+    return guarded([&]() -> trt_status {
+        if (batch_names_automatic(b, l)) {
+            l.waves_per_block = l.steps_per_sweep = l.prefetch_rows = 0;
+            if (l.xcd_remap == kBatchDefaultLaunch.xcd_remap) l.remap_asked = 0;
+        }
+        b->launch = l;
+        return batch_build(b);
+    });
 }
 
 // Host state of the members after `steps` time steps in which class-0

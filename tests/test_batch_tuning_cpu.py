@@ -69,3 +69,35 @@ def requests():
 
 def test_a_set_field_asks_for_the_passes_it_describes(tmp_path):
     host_hip.in_process("test_batch_tuning_cpu", "requests", str(tmp_path))
+
+
+def round_trip():
+    capi = host_hip.capi
+    for name in BATCHES:
+        for kw in (dict(), dict(graph_steps=8), dict(batch_order=2), dict(xcd_remap=1)):
+            a, b = _batch(name), _batch(name)
+            capi.trt_batch_set_tuning(a, **kw)
+            capi.trt_batch_set_tuning(b, **kw)
+            shape = capi.trt_batch_get_tuning(b)
+            capi.trt_batch_set_tuning(b, *shape)
+            assert capi.trt_batch_get_tuning(b) == shape, (name, kw)
+            assert _step(b, 7) == _step(a, 7), (name, kw)
+            fresh = _batch(name)          # read from one batch, set on another
+            capi.trt_batch_set_tuning(fresh, *shape)
+            assert capi.trt_batch_get_tuning(fresh) == shape
+        # the default's six leading fields, as the tuner names it
+        b = _batch(name)
+        capi.trt_batch_set_tuning(b, 0, 4, 0, 0, -1, 1)
+        assert _step(b) == _step(_batch(name)), name
+    # one field off: the passes that the fields describe
+    b = _batch("f64 two steps")
+    shape = list(capi.trt_batch_get_tuning(b))
+    for field, value in ((1, 2), (7, 1), (8, 1)):
+        off = list(shape)
+        off[field] = value
+        capi.trt_batch_set_tuning(b, *off)
+        assert not _new_passes(b), (field, value)
+
+
+def test_a_reported_shape_set_again_keeps_the_passes(tmp_path):
+    host_hip.in_process("test_batch_tuning_cpu", "round_trip", str(tmp_path))
