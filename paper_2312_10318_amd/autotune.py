@@ -64,13 +64,20 @@ def _bucket(v: int) -> int:
     return 1 << max(6, min(15, int(round(math.log2(max(1, v))))))
 
 
+# Part of every cache key: which passes the library has and what a shape asks for.
+# A shape cached under other rules names passes that may no longer be the best
+# (128^2 FP64: the best one-step shape 3.5 us per step, the library's own 2.7), so
+# it goes up with them.
+RULES = 2
+
+
 def key(nx: int, ny: int, storage: str, has_mask: bool, arch: str = "gfx950",
         walls: bool = False) -> str:
     """Cache key: storage, the lattice's kind (open; a mask whose solid
-    nodes fill whole rows, walls; any other mask or open x boundaries) and
-    the size buckets."""
+    nodes fill whole rows, walls; any other mask or open x boundaries),
+    the size buckets and the rules (RULES)."""
     kind = ("walls" if walls else "mask") if has_mask else "open"
-    return "%s|%s|%s|%d|%d" % (arch, storage, kind, _bucket(nx), _bucket(ny))
+    return "%s|%s|%s|%d|%d|rules%d" % (arch, storage, kind, _bucket(nx), _bucket(ny), RULES)
 
 
 def row_walls(mask, inflow=None) -> bool:
@@ -237,7 +244,8 @@ def best_shape(nx: int, ny: int, storage: str = "f32", has_mask: bool = False,
 # column mode.  Row policies (trt_tuning.batch_items): -1 each member's own
 # automatic rows; n > 0 one batch-wide cap leaving at least n work items
 # (members no taller than the cap in one item per strip).  Orders
-# (batch_order): 1 member by member, 2 costliest items first.
+# (batch_order): 1 member by member, 2 costliest items first.  (0, 4, 0, 0, -1, 1)
+# names the library's own choice, some of whose passes take no other shape.
 BATCH_ROWS = (4, 8, 16, 32)
 BATCH_WAVES = (2, 4)
 BATCH_ITEMS = (-1, 16384, 32768)
@@ -255,16 +263,16 @@ def batch_candidates():
 
 
 def batch_key(sizes, storage: str, has_mask: bool, arch: str = "gfx950") -> str:
-    """Cache key of a batch: storage, mask presence, member count and the
+    """Cache key of a batch: storage, mask presence, member count, the
     members' node counts in power-of-two buckets (the shape of the work, not
-    its exact sizes)."""
+    its exact sizes) and the rules (RULES)."""
     hist = {}
     for nx, ny in sizes:
         b = _bucket(int(round(math.sqrt(max(1, nx * ny)))))
         hist[b] = hist.get(b, 0) + 1
     comp = ",".join("%dx%d" % (b, hist[b]) for b in sorted(hist))
-    return "%s|%s|%s|batch|%d|%s" % (arch, storage, "mask" if has_mask else "open",
-                                     len(sizes), comp)
+    return "%s|%s|%s|batch|%d|%s|rules%d" % (arch, storage, "mask" if has_mask else "open",
+                                             len(sizes), comp, RULES)
 
 
 def time_batch_shape(batch, shape, steps: int, warmup: int) -> float:
