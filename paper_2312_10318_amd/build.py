@@ -45,6 +45,12 @@ def spills(remarks: str) -> dict:
     return out
 
 
+def spilled_sweeps(remarks: str) -> dict:
+    """The kernels of the step path (and the probe) among those that spill."""
+    return {k: n for k, n in spills(remarks).items()
+            if n > 0 and any(part in k for part in ("sweep", "probe", "narrow", "resident"))}
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source into paper_2312_10318_amd/libtrtlbm.so."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
@@ -56,8 +62,7 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise RuntimeError("hipcc failed building libtrtlbm.so")
-    spilled = {k: n for k, n in spills(r.stderr).items()
-               if n > 0 and ("sweep" in k or "probe" in k or "narrow" in k)}
+    spilled = spilled_sweeps(r.stderr)
     if spilled:
         os.remove(tmp)
         raise RuntimeError("sweep kernels spill registers to scratch memory: %s" % spilled)

@@ -29,6 +29,7 @@ import re
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SWEEP_SOURCES = ["paper_2312_10318_amd/csrc/sweep.hip", "paper_2312_10318_amd/csrc/lattice.hpp",
                  "paper_2312_10318_amd/csrc/narrow.hip", "paper_2312_10318_amd/csrc/wave.hpp",
+                 "paper_2312_10318_amd/csrc/resident.hip",
                  "paper_2312_10318_amd/csrc/kernels.hpp", "paper_2312_10318_amd/csrc/probe.hip"]
 COPY_BYTES = 1 << 30
 BYTES_PER_LU = {"f64": 144, "f32": 72, "f16": 36}
@@ -66,16 +67,24 @@ def _is_sweep(name):
             "sweep_tb3_kernel" in name or "sweep_tb3_batch_kernel" in name or
             "sweep_batch_kernel" in name or
             "narrow_kernel" in name or "narrow_batch_kernel" in name or
+            "resident_kernel" in name or "resident_batch_kernel" in name or
             "pattern_probe_kernel" in name)
 
 
-def updates_per_launch(kernel_name) -> int:
-    """Time steps one launch of a sweep kernel advances the lattice by."""
+def updates_per_launch(kernel_name, steps_per_dispatch=None) -> int:
+    """Time steps one launch of a sweep kernel advances the lattice by (the
+    resident kernels: as many as the run's steps make per dispatch)."""
     name = kernel_name or ""
+    if _is_resident(name):
+        return steps_per_dispatch
     narrow = re.search(r"narrow(?:_batch)?_kernel<\d, (\d)", name)
     if narrow:
         return int(narrow.group(1))
     return 3 if "sweep_tb3" in name else 2 if "sweep_tb2" in name else 1
+
+
+def _is_resident(name):
+    return "resident_kernel" in name or "resident_batch_kernel" in name
 
 
 def _is_copy(name):
@@ -191,7 +200,10 @@ def summarize(trace_dir, fetch_dir, write_dir, storage, n, steps, warmup, out_pr
     sweep_ns, copy_ns, kname = kernel_durations(trace_dir)
     fs, fc = counter_values(fetch_dir, "FETCH_SIZE", kname)
     ws, wc = counter_values(write_dir, "WRITE_SIZE", kname)
-    # the first dispatches include cold-cache and launch warm-up effects
+    # the first dispatches include cold-cache and launch warm-up effects; a
+    # resident run may hold no others, as one takes all the steps of a call
+    if _is_resident(kname or ""):
+        skip_first = 0
     sweep_ns, fs, ws = sweep_ns[skip_first:], fs[skip_first:], ws[skip_first:]
     avg = lambda v: sum(v) / len(v)
     fetch_scale = COPY_BYTES / (avg(fc) * 1024.0)
@@ -208,11 +220,11 @@ def summarize(trace_dir, fetch_dir, write_dir, storage, n, steps, warmup, out_pr
         label, wlabel = title % (n, n), wname % (n, n)
     # 9 populations read and written (+ the link code read, with a link map)
     # per lattice update; a two-step launch counts two updates per node
-    ups = updates_per_launch(kname)
+    ups = updates_per_launch(kname, (warmup + steps) // max(1, len(sweep_ns)))
     alg = (BYTES_PER_LU[storage] + link_bytes) * nodes * ups
     dur = avg(sweep_ns) * 1e-9
     rec = {
-        "kernel": (re.search(r"(sweep_(single|pair|tb2_batch|tb2|tb3_batch|tb3|batch)|narrow_batch|narrow|pattern_probe)_kernel(<[^>]*>)?",
+        "kernel": (re.search(r"(sweep_(single|pair|tb2_batch|tb2|tb3_batch|tb3|batch)|narrow_batch|narrow|resident_batch|resident|pattern_probe)_kernel(<[^>]*>)?",
                              kname or "") or re.search(r".*", "sweep")).group(0),
         "workload": wlabel, "storage": storage, "nodes": nodes, "updates_per_launch": ups,
         "source_hash": _run_hash(run_log) if run_log else sweep_source_hash(),
