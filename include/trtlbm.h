@@ -364,10 +364,11 @@ trt_status trt_batch_create(int32_t n, trt_sim *const *sims, trt_batch **out);
  * the new tables are copied on the batch's stream behind them, from one of
  * a ring of pinned staging buffers, and the call waits at most for the copy
  * that last used that buffer (several updates earlier).  Serving uses this
- * at every change of the active set.  An update that fails for want of memory
- * (ENOMEM, EDEVICE) has replaced the members all the same: trt_batch_diagnostics
- * works, and trt_batch_step returns ESTATE until an update or a change of the
- * launch shape succeeds (whose own failure leaves the batch in that state too). */
+ * at every change of the active set.  An update that fails leaves the members as
+ * they were.  Where it failed for want of memory (ENOMEM, EDEVICE),
+ * trt_batch_diagnostics works and trt_batch_step returns ESTATE until an update
+ * or a change of the launch shape succeeds (whose own failure leaves the batch in
+ * that state too). */
 trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims);
 
 /* Advance every member nsteps steps (replays of captured graphs of batched

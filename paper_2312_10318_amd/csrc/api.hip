@@ -1312,17 +1312,17 @@ static trt_status check_members(int32_t n, trt_sim *const *sims, const trt_batch
     return TRT_OK;
 }
 
-static void batch_set_members(trt_batch *b, int32_t n, trt_sim *const *sims) {
-    std::vector<trt_sim *> next(sims, sims + n);  // may throw: nothing changed yet
+// The batch's members become `members`, which takes the former ones.
+static void batch_swap_members(trt_batch *b, std::vector<trt_sim *> &members) noexcept {
     for (trt_sim *m : b->sims) m->in_batch = false;
-    b->sims.swap(next);
-    b->storage = sims[0]->prob.storage;
+    b->sims.swap(members);
     b->mask = false;
     b->buf = true;
-    for (int k = 0; k < n; ++k) {
-        b->mask = b->mask || sims[k]->prob.mask != nullptr || sims[k]->prob.x_boundary != 0;
-        b->buf = b->buf && trt::buffer_addressable(sims[k]->desc, sims[k]->prob.storage);
-        sims[k]->in_batch = true;
+    for (trt_sim *m : b->sims) {
+        b->storage = m->prob.storage;
+        b->mask = b->mask || m->prob.mask != nullptr || m->prob.x_boundary != 0;
+        b->buf = b->buf && trt::buffer_addressable(m->desc, m->prob.storage);
+        m->in_batch = true;
     }
 }
 
@@ -1340,7 +1340,8 @@ trt_status trt_batch_create(int32_t n, trt_sim *const *sims, trt_batch **out) {
         for (auto &sg : b->stage)
             if (e == hipSuccess) e = hipEventCreateWithFlags(&sg.done, hipEventDisableTiming);
         if (e != hipSuccess) return fail_hip(e, "batch stream/event");
-        batch_set_members(b, n, sims);
+        std::vector<trt_sim *> members(sims, sims + n);
+        batch_swap_members(b, members);
         return batch_build(b);
     });
     if (st != TRT_OK) {
@@ -1356,8 +1357,11 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims) {
         if (!b) return fail(TRT_EINVAL, "batch handle is NULL");
         trt_status st = check_members(n, sims, b);
         if (st != TRT_OK) return st;
-        batch_set_members(b, n, sims);
-        return batch_build(b);
+        std::vector<trt_sim *> members(sims, sims + n);  // may throw: nothing changed yet
+        batch_swap_members(b, members);
+        st = guarded([&] { return batch_build(b); });
+        if (st != TRT_OK) batch_swap_members(b, members);
+        return st;
     });
 }
 

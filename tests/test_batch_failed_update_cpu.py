@@ -1,7 +1,8 @@
-"""A batch whose membership or launch shape could not be rebuilt (no memory for
-the device tables or for their staging): its diagnostics are still every member's
-own, it refuses to step until a rebuild succeeds, and no launch names a table that
-is missing or holds other members."""
+"""A membership change that fails for want of memory (for the device tables or for
+their staging): the batch keeps its members, whose diagnostics are still their own
+and as many as its caller has room for; it refuses to step until a rebuild succeeds,
+no launch names a table that is missing or holds other members, and the simulations
+that did not join are free."""
 import pytest
 
 import host_hip
@@ -20,11 +21,13 @@ def _check(fail):
     host_hip.clear()
     capi.trt_batch_diagnostics(b, 4096)
     got = [(w, s) for k, w, s in host_hip.launches() if "final" not in k]
-    assert got == [(a, 0) for _, a in large]   # each from its own descriptor and lattice
+    assert got == [(a, 1) for _, a in small]   # each from its own descriptor and lattice
     host_hip.clear()
     assert host_hip.status(lambda: capi.trt_batch_step(b, 3)) == capi.TRT_ESTATE
     assert host_hip.launches() == []
-    capi.trt_batch_update(b, [h for h, _ in small])
+    assert host_hip.status(lambda: capi.trt_step(small[0][0], 1)) == capi.TRT_ESTATE
+    capi.trt_step(large[0][0], 1)
+    capi.trt_batch_update(b, [h for h, _ in large])
     capi.trt_batch_diagnostics(b, 4096)
     capi.trt_batch_step(b, 3)
     assert host_hip.launches() and all(w != 0 for _, w, _ in host_hip.launches())
