@@ -167,8 +167,8 @@ WORKLOADS = {
 }
 
 
-SQ_COUNTERS = ("SQ_WAVES", "SQ_INSTS_VALU", "SQ_ACTIVE_INST_VALU", "SQ_WAVE_CYCLES",
-               "SQ_WAIT_INST_ANY", "GRBM_GUI_ACTIVE")
+SQ_COUNTERS = ("SQ_WAVES", "SQ_INSTS_VALU", "SQ_INSTS_SALU", "SQ_INSTS_SMEM", "SQ_INSTS_VMEM",
+               "SQ_ACTIVE_INST_VALU", "SQ_WAVE_CYCLES", "SQ_WAIT_INST_ANY", "GRBM_GUI_ACTIVE")
 SIMDS = 1024  # 256 CUs x 4 SIMDs
 XCDS = 8
 
@@ -191,6 +191,10 @@ def sq_summary(sq_dir, kernel, skip_first=2):
         out["valu_busy_frac"] = round(vals["SQ_INSTS_VALU"] * 4 / (SIMDS * cycles), 4)
     if "SQ_WAIT_INST_ANY" in vals and "SQ_WAVE_CYCLES" in vals:
         out["wave_wait_frac"] = round(vals["SQ_WAIT_INST_ANY"] / vals["SQ_WAVE_CYCLES"], 4)
+    insts = ["SQ_INSTS_VALU", "SQ_INSTS_SALU", "SQ_INSTS_SMEM", "SQ_INSTS_VMEM"]
+    if all(k in vals for k in insts + ["SQ_WAVES", "SQ_WAVE_CYCLES"]):
+        out["instructions_per_wave"] = round(sum(vals[k] for k in insts) / vals["SQ_WAVES"], 1)
+        out["cycles_per_wave"] = round(4 * vals["SQ_WAVE_CYCLES"] / vals["SQ_WAVES"], 1)
     return out
 
 
@@ -287,7 +291,9 @@ def summarize(trace_dir, fetch_dir, write_dir, storage, n, steps, warmup, out_pr
         if sq_dir:
             fh.write("\nvalu_busy_frac: VALU instructions x 4 cycles / (1024 SIMDs x busy "
                      "cycles per XCD); wave_wait_frac: SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES "
-                     "(the share of the wavefronts' lifetime spent waiting to issue).\n")
+                     "(the share of the wavefronts' lifetime spent waiting to issue); "
+                     "cycles_per_wave: 4 x SQ_WAVE_CYCLES / SQ_WAVES (the counter steps every "
+                     "fourth cycle), the lifetime of a wavefront.\n")
         stats = _csv(trace_dir, "kernel_stats.csv")
         fh.write("\n`--kernel-trace --stats` summary (durations in ns):\n\n")
         fh.write("| kernel | calls | average | min | max |\n|---|---|---|---|---|\n")
