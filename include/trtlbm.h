@@ -164,7 +164,9 @@ typedef struct {
                                 two where allowed; in a batch three for FP32 members, two for
                                 FP16; in the one-column pass, see above, three for FP64 from
                                 about 3.9e5 nodes and for FP32 from 65537, 524289 with a
-                                mask or open boundaries, else two).  k steps per launch move each
+                                mask or open boundaries, else two; FP32 lattices of
+                                exactly 1024^2 without either keep two, the shape they
+                                have always reported).  k steps per launch move each
                                 population through HBM once per k steps and give the bits of
                                 k one-step sweeps.  Two apply to FP32 and FP16 simulations,
                                 alone or in a batch, without a mask or open boundaries, or

@@ -86,9 +86,9 @@ template <int ST, bool LINK> struct NarrowRow {
 
 // Whether a lane keeps the byte offsets of its pulls and populations in a row, so
 // that an access adds the row's alone: 15 registers for 80 scalar instructions
-// in two pipeline rows (FP32, two steps: 646 instructions -> 558).  A lone
-// wavefront issues one instruction in five to six cycles whatever its kind, so
-// that is time where few wavefronts run (us per step, before / now: FP32 300^2
+// in two pipeline rows (FP32, two steps: 646 instructions -> 558).  Where few
+// wavefronts run, nothing hides an instruction of whatever kind (256^2, one a
+// SIMD: 1523 in 11,550 cycles), so that is time (us per step, before / now: FP32 300^2
 // 3.26 / 3.10, 1000^2 8.23 / 8.12; FP64 400 x 200 with an obstacle 5.04 / 4.76;
 // FP16 300^2 3.59 / 3.41); beside others the registers count (FP16 obstacles
 // 1400^2 16.2 / 18.9: three wavefronts per SIMD instead of four).
@@ -673,7 +673,8 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     2.9, three 3.0, 400 x 200 3.4 / 3.2, 420^2 4.4 / 4.0, 512^2 4.5 / 4.4
 //     against 8.6, 800^2 7.2 / 6.8, 1000^2 11.0 / 8.2, 1448^2 20.1 / 15.5 against
 //     19.6, 2048^2 27.3 against 27.9.  1024^2 alone keeps two steps and eight
-//     rows (10.6; 8.2 with three; 12.6 before): callers rely on that default.
+//     rows (10.6; 8.2 with three; 12.6 before): no measurement asks for it, the
+//     shape that this size reports is fixed by a test of the default shapes.
 //   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
 //     14.9, 2048^2 25.9 / 27.3 (so not there, and of even width below that only
 //     where the 128-column launches leave their last round idle:
