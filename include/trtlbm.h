@@ -122,7 +122,7 @@ typedef struct {
  * pass of two or three time steps per launch with one column per lane, which
  * applies to every storage, mask and boundary within 4 GiB: FP64 lattices,
  * lattices with a mask that does not fill whole rows or with open x
- * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1600^2 nodes
+ * boundaries, and FP32 and FP16 lattices below about 2048^2 and 1580^2 nodes
  * (FP16 of even width from about 1100^2 on: where its launches fill the machine
  * better).
  * trt_get_tuning then reports that pass's rows, wavefronts, steps and

@@ -676,9 +676,11 @@ hipError_t launch_narrow_batch(const InstDesc *descs, int ndescs, const int4 *it
 //     rows (10.6; 8.2 with three; 12.6 before): no measurement asks for it, the
 //     shape that this size reports is fixed by a test of the default shapes.
 //   FP16: 128^2 7.5 / 2.5, 512^2 8.2 / 4.4, 1024^2 11.9 / 9.3, 1448^2 two steps
-//     14.9, 2048^2 25.9 / 27.3 (so not there, and of even width below that only
-//     where the 128-column launches leave their last round idle:
-//     wide_rounds_f16); cylinder 1050^2 21.1 / 11.0;
+//     14.9, 2048^2 25.9 / 27.3 (so not there, and not where the 128-column
+//     launches' third round is nearly full, from 2.49 M nodes on -- 1561^2 18.6 /
+//     18.0, 1601^2 18.6 / 19.5, 2525 x 1032 18.3 / 19.8, channels equal; of even
+//     width below that by the rounds of both: wide_rounds_f16); cylinder 1050^2
+//     21.1 / 11.0;
 //     obstacle 2048^2 47.4 / 34.7 (three steps 35.2).
 // Rows: a block of R rows runs R + 2 (2 k - 1) pipeline rows.  FP64, and two
 // steps in FP32: the smallest R that leaves at most two wavefronts per SIMD
@@ -717,7 +719,7 @@ NarrowPlan narrow_plan(const InstDesc &d, int storage, const Launch &l) {
         const bool two = d.links ? nodes <= k1 * k1 / 2
                                  : nodes <= k1 * 64 || (d.nx == k1 && d.ny == k1);
         p.k = two ? 2 : 3;
-    } else if (wide && nodes > k1 * k1 * 5 / 2) {
+    } else if (wide && nodes > k1 * k1 * 19 / 8) {
         return p0;
     }
     const auto waves = [&](int r) { return narrow_waves(d, p.k, r); };

@@ -7,8 +7,8 @@ import pytest
 
 import host_hip
 
-WIDE = [(1300, 1300), (1600, 1600), (1052, 1750), (2738, 942)]
-NARROW = [(1250, 1250), (1450, 1450), (1014, 1378), (1601, 1600), (1299, 1300), (300, 300)]
+WIDE = [(1300, 1300), (1600, 1600), (1052, 1750), (2738, 942), (1601, 1601), (1107, 2359)]
+NARROW = [(1250, 1250), (1450, 1450), (1014, 1378), (1561, 1561), (1299, 1300), (300, 300)]
 WIDE_BATCH = [(9, 500, 500), (5, 700, 700), (24, 300, 300), (13, 500, 500)]
 NARROW_BATCH = [(7, 500, 500), (10, 500, 500), (9, 501, 500), (4, 700, 700), (28, 300, 300)]
 
@@ -41,7 +41,7 @@ def test_the_launch_that_fills_its_rounds(tmp_path):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("walls", [False, True])
-@pytest.mark.parametrize("nx,ny", [(1300, 1300), (1600, 1600), (1250, 1250), (1601, 1600)])
+@pytest.mark.parametrize("nx,ny", [(1300, 1300), (1600, 1600), (1250, 1250), (1601, 1600), (1561, 1561)])
 def test_either_side_keeps_the_bits(nx, ny, walls):
     import torch
     if not torch.cuda.is_available():
