@@ -88,7 +88,7 @@ template <int ST, bool LINK> struct NarrowRow {
 // that an access adds the row's alone: 15 registers for 80 scalar instructions
 // in two pipeline rows (FP32, two steps: 646 instructions -> 558).  Where few
 // wavefronts run, nothing hides an instruction of whatever kind (256^2, one a
-// SIMD: 1523 in 11,550 cycles), so that is time (us per step, before / now: FP32 300^2
+// SIMD: 1523 in 11,500 cycles), so that is time (us per step, before / now: FP32 300^2
 // 3.26 / 3.10, 1000^2 8.23 / 8.12; FP64 400 x 200 with an obstacle 5.04 / 4.76;
 // FP16 300^2 3.59 / 3.41); beside others the registers count (FP16 obstacles
 // 1400^2 16.2 / 18.9: three wavefronts per SIMD instead of four).
