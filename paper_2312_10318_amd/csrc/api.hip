@@ -252,9 +252,9 @@ struct trt_batch {
     int nnarrow[2]; // items of 64-column windows without, with a link map
     int nresident, resident_nodes;  // resident members, the largest one's nodes
     int ndescs2;    // descriptors tiled for launches of several steps
-    size_t diag_at;
+    size_t diag_at; // where the members' MemberDiag entries begin
     bool deep2;     // two-step launches of 128-column windows load two rows ahead
-    bool deep;      // and launches of either kind of windows do
+    bool deep;      // some launch of several steps, of either windows, does
     bool multi;     // some member takes several steps per launch
     int k2;         // how many: 2 or 3
     int64_t steps;  // time steps since the tables were built
@@ -1367,9 +1367,9 @@ trt_status trt_batch_update(trt_batch *b, int32_t n, trt_sim *const *sims) {
 
 // Whether l names, field by field, what the automatic shape reports for the
 // batch's members (the steps and rows ahead may be left open): set again, a
-// reported shape keeps the passes it came from.  (us per
-// step, read as a request for the passes those fields describe / as the automatic
-// shape: ten FP64 lattices of 4 x 34 6.6 / 0.62, 16 of 128^2 13.4 / 5.7.)
+// reported shape keeps the passes it came from.  (us per step, read as a request for
+// the passes those fields describe / as the automatic shape: ten FP64 lattices of
+// 4 x 34 6.6 / 0.62, 16 of 128^2 13.4 / 5.7.)
 static bool batch_names_automatic(trt_batch *b, const Launch &l) {
     if (l.rows_per_wave != 0 || l.cols_per_lane != 0 || l.batch_items > 0 || !l.remap_asked ||
         l.waves_per_block != trt::batch_waves_per_block(kBatchDefaultLaunch))

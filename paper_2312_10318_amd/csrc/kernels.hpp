@@ -248,10 +248,11 @@ NarrowRows narrow_rows(int storage, int k, bool links, int64_t nodes, W waves) {
 // 16.3, 1600^2 19.3 / 16.6, 1052 x 1750 14.9 / 13.1, channels 1450^2 15.3 / 17.7,
 // 1600^2 20.0 / 18.0; 7 lattices of 500^2 13.5 / 16.6, 9 18.1 / 16.8, 10 19.5 /
 // 21.9; 5 of 700^2 19.5 / 16.9, channels 19.9 / 18.2.  The costs from which one,
-// two, three and four rounds win were read off 210 lattices and batches: the
-// faster pass, or within 2% of it, at all but seven of them (5%).  Odd widths cost the
-// 128-column pass 1.5 to 2 us more, and there the 64-column one always won (1563 x
-// 1311 16.7 / 18.1; 36 lattices of 64 to 600 columns 23.5 / 29.5).
+// two, three and four rounds win were read off 212 lattices and batches: the
+// faster pass, or within 2% of it, at all but five of them (5%).  Odd widths cost the
+// 128-column pass 1.5 to 2 us more, and below 2.49 M nodes the 64-column one was the
+// faster there but for a few in the last 2% (1563 x 1311 16.7 / 18.1; 36 lattices of
+// 64 to 600 columns 23.5 / 29.5).
 inline bool wide_rounds_f16(int64_t wide, int64_t cost, bool links) {
     constexpr int from[2][4] = {{49, 73, 98, 136}, {133, 201, 269, 337}};
     const int64_t n = (wide + 1023) / 1024;
